@@ -32,13 +32,16 @@
 // (four waves per SIMD at 16 points per thread) and by the reduction chain
 // for small P.
 //
-// From 513 to 8192 points fps_lds_kernel keeps a copy of the coordinates
-// in LDS as well, so the winners are exchanged as (distance, index) and the
-// new centroid is read from LDS after the block reduction; from 8193 to
-// 16384 points fps_skip_kernel orders the cloud spatially and skips the
-// updates that provably change nothing; above 32768 points fps_multi_kernel
-// spreads a cloud over several workgroups.
+// 128 and more samples of 257 to 16384 points: fps_rounds_kernel, which
+// selects many samples per exchange.  Fewer samples: from 513 to 8192 points
+// fps_lds_kernel keeps a copy of the coordinates in LDS as well, so the
+// winners are exchanged as (distance, index) and the new centroid is read from
+// LDS after the block reduction; from 8193 to 16384 points fps_skip_kernel
+// orders the cloud spatially and skips the updates that provably change
+// nothing.  Above 32768 points fps_multi_kernel spreads a cloud over several
+// workgroups.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 
@@ -658,6 +661,591 @@ static void launch_fps_skip(const float* xyz, int64_t B, int N, int M, int32_t* 
     fps_skip_kernel<T, P><<<dim3((unsigned)B), dim3(T), 0, s>>>(xyz, N, M, idx, cxyz);
 }
 
+// ---------------------------------------------------------------------------
+// Several samples per round.
+//
+// One sample per iteration leaves the chip waiting on a serial chain (update,
+// wave maximum, LDS exchange, barrier, block maximum, new centroid).  Here a
+// round selects every sample that the state at its start already decides:
+//
+//  * every point whose running minimum is above a threshold is a candidate.
+//    All other points are at most the threshold, and running minima only
+//    fall, so as long as the best candidate -- its value lowered by the
+//    samples chosen meanwhile -- is above the threshold, it is the next
+//    sample (equal values: the lowest index);
+//  * the candidates are compared pairwise: one that no earlier candidate
+//    (larger value, then lower index) lowers keeps its value and its place in
+//    the order.  One that is lowered raises the threshold to its lowered
+//    value (or, where a candidate that lowers it is itself lowered, to its
+//    own).  The unlowered candidates above that are the next samples, in
+//    order; the first is always among them;
+//  * the threshold of the next round lies a little below this one's, by a
+//    fraction that follows the number of candidates found (about 22 are
+//    wanted; 13 of them become samples).  With none, or with more than are
+//    kept, the round selects nothing and the next one selects the maximum, as
+//    the first rounds do, whose values fall too fast to predict.  Where many
+//    points share the maximum the threshold is that value and an index;
+//  * the points are put in spatial order: slabs of equal count along the
+//    cloud's longest axis, each sorted along the second longest.  64
+//    consecutive points form a row, and a row is one register of one wave
+//    (lane l holds point l).  RG consecutive rows form a block; consecutive
+//    blocks go to different waves.  A block is updated
+//    with a sample only when the lower bound of the distance from the sample
+//    to the block's box is below the cloud's largest running minimum.  The
+//    bound is formed by the distance's own operations on the per-axis gaps
+//    max(lo - c, c - hi, 0): every operation is monotone and each gap is at
+//    most the rounded |point - c|, so a skipped update changes nothing.
+// So the samples are those of one-at-a-time selection, bit for bit.
+//
+// A round has two barriers: the waves collect the candidates, share the
+// pairwise comparison, and then each derives the samples by itself.  It is
+// bound by instruction issue on the cloud's one CU (about 2900 cycles at 1024
+// points for 12 samples: update 700, collecting and its imbalance 900,
+// comparison 600, choice 700).  Measured, one launch, against one sample per
+// iteration: 32 x 1024 -> 512 160 -> 74 us, 16 x 4096 -> 1024 476 -> 154 us,
+// 3 x 5003 -> 1251 816 -> 192 us, 4 x 16384 -> 4096 (LiDAR) 3.46 -> 0.74 ms.
+// Clouds on an integer grid (most values tied): 1024 -> 700 215 -> 122 us.
+// ---------------------------------------------------------------------------
+
+constexpr int kFpsBins = 4096;             // bins of each pass of the sort
+constexpr int kFpsSingle = 16;             // samples selected one at a time at first
+constexpr int kFpsPad = (int)0xbf800000;   // -1.0f, a padding point's running minimum: never selected
+
+__device__ __forceinline__ float lane_f32(float v, int l) {
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+}
+
+// The value in a vector register (what a NaN coordinate's differences become
+// depends on the operand's place).
+__device__ __forceinline__ float to_vgpr(float v) {
+    float r;
+    asm("v_mov_b32 %0, %1" : "=v"(r) : "s"(v));
+    return r;
+}
+
+__device__ __forceinline__ int wave_min_i32(int v) { return ~wave_max_i32(~v); }
+
+template <int T, int P, int RG>
+__global__ __launch_bounds__(T) void fps_rounds_kernel(const float* __restrict__ xyz, int N, int M,
+                                                       int32_t* __restrict__ idx, float* __restrict__ cxyz) {
+    constexpr int W = T / 64;
+    constexpr int NP = T * P;
+    constexpr int CAP = 32;                // candidates compared (and samples) per round
+    constexpr int KEEP = 64;               // candidates kept per round
+    constexpr int NB = P / RG;             // blocks per wave
+    constexpr bool XY = NP > 8192;         // only x and y fit in LDS
+    constexpr int CPT = kFpsBins / T;
+    static_assert(kFpsBins % T == 0 && W <= 16 && P % RG == 0 && NB <= 4, "shape");
+    constexpr int kCoord = (XY ? 2 : 3) * NP * 4;
+    constexpr int kSort = NP * 2 + kFpsBins * 4;
+    __shared__ __attribute__((aligned(16))) char s_mem[XY ? (kCoord > kSort ? kCoord : kSort) : kCoord + kSort];
+    __shared__ float4 s_ent[2][KEEP];      // candidates: x, y, z, running minimum
+    __shared__ int s_eix[2][KEEP];         // their indices' complements
+    __shared__ float4 s_list[CAP];         // the largest of more than CAP
+    __shared__ int s_lidx[CAP];
+    __shared__ int s_cnt[3];               // candidates found, by round % 3
+    __shared__ int2 s_pair[CAP];           // per candidate: those ahead of it, those lowering it
+    __shared__ int s_low[2][CAP];          // its value lowered by them, by round % 2
+    __shared__ int2 s_best[2][W];          // single rounds: each wave's largest value, its index
+    __shared__ float s_red[6][W];
+    __shared__ int s_wsum[W];
+    float* s_c = reinterpret_cast<float*>(s_mem);                          // by original index
+    uint16_t* s_perm = reinterpret_cast<uint16_t*>(s_mem + (XY ? 0 : kCoord));
+    int* s_hist = reinterpret_cast<int*>(s_mem + (XY ? 0 : kCoord) + NP * 2);
+    uint16_t* s_out = s_perm;              // the selected indices (not with XY)
+
+    const int b = blockIdx.x;
+    const float* __restrict__ p = xyz + (int64_t)b * N * 3;
+    int32_t* __restrict__ out_idx = idx + (int64_t)b * M;
+    float* __restrict__ out_c = cxyz ? cxyz + (int64_t)b * M * 3 : nullptr;
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const float inf = __builtin_huge_valf();
+
+    float px[P], py[P], pz[P];
+    int dm[P];                             // running minima as bits (>= 0, or the sentinel)
+    unsigned oi[(P + 1) / 2];              // original indices, two in a word
+    auto index = [&](int q) { return (int)(oi[q / 2] >> (16 * (q & 1))) & 0xffff; };
+    auto set_index = [&](int q, int j) { oi[q / 2] = q & 1 ? (oi[q / 2] & 0xffffu) | ((unsigned)j << 16) : (unsigned)j; };
+    {
+        // 1. the cloud's box
+        float mnx = inf, mny = inf, mnz = inf, mxx = -inf, mxy = -inf, mxz = -inf;
+#pragma unroll
+        for (int q = 0; q < P; ++q) {
+            const int j = tid + q * T;
+            const bool ok = j < N;
+            const int jj = ok ? j : 0;
+            px[q] = p[3 * jj + 0];
+            py[q] = p[3 * jj + 1];
+            pz[q] = p[3 * jj + 2];
+            mnx = fminf(mnx, px[q]); mxx = fmaxf(mxx, px[q]);
+            mny = fminf(mny, py[q]); mxy = fmaxf(mxy, py[q]);
+            mnz = fminf(mnz, pz[q]); mxz = fmaxf(mxz, pz[q]);
+            if constexpr (!XY) {
+                if (ok) {
+                    s_c[3 * j + 0] = px[q];
+                    s_c[3 * j + 1] = py[q];
+                    s_c[3 * j + 2] = pz[q];
+                }
+            }
+        }
+        mnx = wave_min_f32(mnx); mny = wave_min_f32(mny); mnz = wave_min_f32(mnz);
+        mxx = wave_max_f32(mxx); mxy = wave_max_f32(mxy); mxz = wave_max_f32(mxz);
+        if (lane == 0) {
+            s_red[0][wave] = mnx; s_red[1][wave] = mny; s_red[2][wave] = mnz;
+            s_red[3][wave] = mxx; s_red[4][wave] = mxy; s_red[5][wave] = mxz;
+        }
+        for (int c = tid; c < kFpsBins; c += T) s_hist[c] = 0;
+        if (tid < 3) s_cnt[tid] = 0;
+        if (tid < CAP) s_low[0][tid] = INT32_MAX;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            mnx = fminf(mnx, s_red[0][w]); mny = fminf(mny, s_red[1][w]); mnz = fminf(mnz, s_red[2][w]);
+            mxx = fmaxf(mxx, s_red[3][w]); mxy = fmaxf(mxy, s_red[4][w]); mxz = fmaxf(mxz, s_red[5][w]);
+        }
+        // 2. the two longest axes (any order of the points keeps the result
+        //    exact, also that of non-finite coordinates)
+        const float ex = mxx - mnx, ey = mxy - mny, ez = mxz - mnz;
+        const int a0 = ex >= ey ? (ex >= ez ? 0 : 2) : (ey >= ez ? 1 : 2);
+        const int a1 = a0 == 0 ? (ey >= ez ? 1 : 2) : a0 == 1 ? (ex >= ez ? 0 : 2) : (ex >= ey ? 0 : 1);
+        const float lo0 = a0 == 0 ? mnx : a0 == 1 ? mny : mnz, ext0 = a0 == 0 ? ex : a0 == 1 ? ey : ez;
+        const float lo1 = a1 == 0 ? mnx : a1 == 1 ? mny : mnz, ext1 = a1 == 0 ? ex : a1 == 1 ? ey : ez;
+        // 3. slabs of equal count along the longest, each of whole blocks,
+        //    about as many as a slab has blocks; bins of the second per slab
+        const int blocks = (N + 64 * RG - 1) / (64 * RG);
+        const int slabs = max(1, (int)(__builtin_sqrtf((float)blocks) + 0.5f));
+        const int slab = (blocks + slabs - 1) / slabs * 64 * RG;
+        const int bins = kFpsBins / slabs;
+        const float inv_slab = 1.0f / (float)slab;
+        const float k0 = ext0 > 0.0f ? (float)kFpsBins / ext0 : 0.0f, k1 = ext1 > 0.0f ? (float)bins / ext1 : 0.0f;
+        // exclusive scan of the counts in place
+        auto scan = [&]() {
+            int cnt[CPT], run = 0;
+#pragma unroll
+            for (int k = 0; k < CPT; ++k) {
+                cnt[k] = s_hist[tid * CPT + k];
+                run += cnt[k];
+            }
+            int incl = run;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const int v = __shfl_up(incl, o);
+                if (lane >= o) incl += v;
+            }
+            if (lane == 63) s_wsum[wave] = incl;
+            __syncthreads();
+            int off = incl - run;
+            for (int w = 0; w < wave; ++w) off += s_wsum[w];
+#pragma unroll
+            for (int k = 0; k < CPT; ++k) {
+                s_hist[tid * CPT + k] = off;
+                off += cnt[k];
+            }
+            __syncthreads();
+        };
+        int bin[P];
+#pragma unroll
+        for (int q = 0; q < P; ++q) {
+            const float c = a0 == 0 ? px[q] : a0 == 1 ? py[q] : pz[q];
+            bin[q] = (int)fminf(fmaxf((c - lo0) * k0, 0.0f), (float)(kFpsBins - 1));
+            if (tid + q * T < N) atomicAdd(&s_hist[bin[q]], 1);
+        }
+        __syncthreads();
+        scan();
+#pragma unroll
+        for (int q = 0; q < P; ++q) {
+            if (tid + q * T < N) bin[q] = atomicAdd(&s_hist[bin[q]], 1);   // place along the longest axis
+        }
+        __syncthreads();
+        for (int c = tid; c < kFpsBins; c += T) s_hist[c] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < P; ++q) {
+            const float c = a1 == 0 ? px[q] : a1 == 1 ? py[q] : pz[q];
+            const int of = min((int)(((float)bin[q] + 0.5f) * inv_slab), slabs - 1);
+            bin[q] = of * bins + (int)fminf(fmaxf((c - lo1) * k1, 0.0f), (float)(bins - 1));
+            if (tid + q * T < N) atomicAdd(&s_hist[bin[q]], 1);
+        }
+        __syncthreads();
+        scan();
+#pragma unroll
+        for (int q = 0; q < P; ++q) {
+            const int j = tid + q * T;
+            if (j < N) s_perm[atomicAdd(&s_hist[bin[q]], 1)] = (uint16_t)j;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < P; ++q) {
+            const int row = ((q / RG) * W + wave) * RG + q % RG;
+            const int pos = row * 64 + lane;
+            set_index(q, pos < N ? (int)s_perm[pos] : 0xffff);
+        }
+        if constexpr (XY) __syncthreads();   // the permutation is read; its space becomes the coordinates
+    }
+    // 5. this lane's points; the boxes of blocks 2 h and 2 h + 1 in the lower and
+    //    upper half of the wave
+    constexpr int NH = (NB + 1) / 2;
+    float bnx[NH], bny[NH], bnz[NH], bxx[NH], bxy[NH], bxz[NH];
+#pragma unroll
+    for (int h = 0; h < NH; ++h) {
+        bnx[h] = bny[h] = bnz[h] = inf;
+        bxx[h] = bxy[h] = bxz[h] = -inf;
+    }
+#pragma unroll
+    for (int k = 0; k < NB; ++k) {
+        float nx = inf, ny = inf, nz = inf, xx = -inf, xy = -inf, xz = -inf;
+#pragma unroll
+        for (int q = k * RG; q < k * RG + RG; ++q) {
+            const bool ok = index(q) != 0xffff;
+            const int j = ok ? index(q) : 0;
+            if constexpr (XY) {
+                px[q] = p[3 * j + 0];
+                py[q] = p[3 * j + 1];
+                pz[q] = p[3 * j + 2];
+                if (ok) {
+                    s_c[2 * j + 0] = px[q];
+                    s_c[2 * j + 1] = py[q];
+                }
+            } else {
+                px[q] = s_c[3 * j + 0];
+                py[q] = s_c[3 * j + 1];
+                pz[q] = s_c[3 * j + 2];
+            }
+            dm[q] = ok ? __float_as_int(inf) : kFpsPad;
+            nx = fminf(nx, ok ? px[q] : inf); xx = fmaxf(xx, ok ? px[q] : -inf);
+            ny = fminf(ny, ok ? py[q] : inf); xy = fmaxf(xy, ok ? py[q] : -inf);
+            nz = fminf(nz, ok ? pz[q] : inf); xz = fmaxf(xz, ok ? pz[q] : -inf);
+        }
+        const bool held = (lane >> 5) == (k & 1);
+        nx = wave_min_f32(nx); bnx[k / 2] = held ? nx : bnx[k / 2];
+        ny = wave_min_f32(ny); bny[k / 2] = held ? ny : bny[k / 2];
+        nz = wave_min_f32(nz); bnz[k / 2] = held ? nz : bnz[k / 2];
+        xx = wave_max_f32(xx); bxx[k / 2] = held ? xx : bxx[k / 2];
+        xy = wave_max_f32(xy); bxy[k / 2] = held ? xy : bxy[k / 2];
+        xz = wave_max_f32(xz); bxz[k / 2] = held ? xz : bxz[k / 2];
+    }
+    __syncthreads();   // the permutation is read: its space becomes the selected indices
+    // the round's samples: lane l holds sample l % 32 where `valid`, the
+    // place-th of `c`
+    const int i = lane & (CAP - 1);
+    float4 s = make_float4(p[0], p[1], p[2], __int_as_float(0));
+    bool valid = i == 0;
+    int place = 0, c = 1, m = 0;
+    int dmax = __float_as_int(inf);   // no running minimum is larger
+    int top = dmax;                   // the same after the samples
+    int tau = 0;                      // the threshold
+    int step = 1 << 19;               // the threshold's next step, in units of the last place
+    int single = kFpsSingle;          // select one sample a round up to this many
+    int tidx = 0, tinc = 0, level = -1;   // tied maxima: candidates at tau itself with lower indices than tidx
+    int now = 0, par = 0;             // round % 3, round % 2
+
+    auto record = [&]() {
+        if (wave == W - 1 && valid && lane < CAP && place < c) {
+            const int o = m + place;
+            if constexpr (XY) {
+                out_idx[o] = __float_as_int(s.w);
+                if (out_c) {
+                    out_c[3 * o + 0] = s.x;
+                    out_c[3 * o + 1] = s.y;
+                    out_c[3 * o + 2] = s.z;
+                }
+            } else {
+                s_out[o] = (uint16_t)__float_as_int(s.w);
+            }
+        }
+        m += c;
+    };
+    // the samples against this wave's blocks
+    auto update = [&]() {
+#pragma unroll
+        for (int h = 0; h < NH; ++h) {
+            const float gx = fmaxf(fmaxf(bnx[h] - s.x, s.x - bxx[h]), 0.0f);
+            const float gy = fmaxf(fmaxf(bny[h] - s.y, s.y - bxy[h]), 0.0f);
+            const float gz = fmaxf(fmaxf(bnz[h] - s.z, s.z - bxz[h]), 0.0f);
+            float lb = gx * gx;
+            lb = __builtin_fmaf(gy, gy, lb);
+            lb = __builtin_fmaf(gz, gz, lb);
+            const uint64_t hit = __builtin_amdgcn_ballot_w64(valid & (__float_as_int(lb) < dmax));
+#pragma unroll
+            for (int k = 2 * h; k < NB && k < 2 * h + 2; ++k) {
+                unsigned left = (unsigned)(hit >> (32 * (k & 1)));
+                while (left) {
+                    const int l = __builtin_ctz(left);
+                    left &= left - 1;
+                    float cx = lane_f32(s.x, l), cy = lane_f32(s.y, l), cz = lane_f32(s.z, l);
+                    if constexpr (NP > 512) {
+                        cx = to_vgpr(cx);
+                        cy = to_vgpr(cy);
+                        if constexpr (!XY) cz = to_vgpr(cz);
+                    }
+#pragma unroll
+                    for (int q = k * RG; q < k * RG + RG; ++q)
+                        dm[q] = min(__float_as_int(dist3(px[q], py[q], pz[q], cx, cy, cz)), dm[q]);
+                }
+            }
+        }
+    };
+    // after a round's first barrier, which every wave reaches only when it has
+    // read what it needs of the round before: clear what the round after the
+    // next one counts into, and the next one's lowered values
+    auto next_round = [&]() {
+        par ^= 1;
+        now = now == 2 ? 0 : now + 1;
+        if (wave == 0) {
+            if (lane == 0) s_cnt[now == 2 ? 0 : now + 1] = 0;
+            if (lane < CAP) s_low[par][lane] = INT32_MAX;
+        }
+    };
+
+    for (;;) {
+        // single rounds: the largest running minimum, the lowest index holding it
+        for (;;) {
+            record();
+            if (m >= M || m >= single) break;
+            update();
+            int b1 = dm[0], bi = index(0);
+#pragma unroll
+            for (int q = 1; q < P; ++q) {
+                const bool up = (dm[q] > b1) | ((dm[q] == b1) & (index(q) < bi));
+                b1 = up ? dm[q] : b1;
+                bi = up ? index(q) : bi;
+            }
+            const int wm = wave_max_i32(b1);
+            const uint64_t at = ballot(b1 == wm);
+            int wi = __builtin_amdgcn_readlane(bi, __builtin_ctzll(at));
+            if (at & (at - 1)) wi = wave_min_i32(b1 == wm ? bi : INT32_MAX);
+            if (lane == 0) s_best[par][wave] = make_int2(wm, wi);
+            __syncthreads();
+            const int2 e = s_best[par][lane & (W - 1)];
+            next_round();
+            const int v = __builtin_amdgcn_readlane(row_max_i32(e.x), 0);
+            const uint64_t eq = ballot(e.x == v) & ((1ull << W) - 1);
+            int sel = __builtin_amdgcn_readlane(e.y, __builtin_ctzll(eq));
+            if (eq & (eq - 1)) sel = wave_min_i32(e.x == v ? e.y : INT32_MAX);
+            if constexpr (XY) {
+                s = make_float4(s_c[2 * sel + 0], s_c[2 * sel + 1], p[3 * sel + 2], __int_as_float(sel));
+            } else {
+                s = make_float4(s_c[3 * sel + 0], s_c[3 * sel + 1], s_c[3 * sel + 2], __int_as_float(sel));
+            }
+            valid = i == 0;
+            place = 0;
+            c = 1;
+            dmax = top = v;
+            // +inf (a coordinate that is not finite, or differences that
+            // overflow) may stay the maximum when selected, which only a
+            // single round gets right
+            if (v == __float_as_int(inf)) single = m + 2;
+            if (tinc > 0 && (level < 0 || v == level)) {
+                level = v;
+                tau = v;
+                tidx = sel + 1 + tinc;
+            } else {
+                tinc = tidx = 0;
+                level = -1;
+                tau = max(v - step, 0);
+            }
+            if (v <= 0) {
+                // every point coincides with a sample: nothing changes any
+                // more, and this one is every further sample
+                if constexpr (XY) {
+                    for (int o = m + tid; o < M; o += T) {
+                        out_idx[o] = sel;
+                        if (out_c) {
+                            out_c[3 * o + 0] = s.x;
+                            out_c[3 * o + 1] = s.y;
+                            out_c[3 * o + 2] = s.z;
+                        }
+                    }
+                } else {
+                    for (int o = m + tid; o < M; o += T) s_out[o] = (uint16_t)sel;
+                }
+                m = M;
+                break;
+            }
+        }
+        if (m >= M) break;
+        // rounds of several samples; at their start no running minimum is
+        // above `dmax` before the samples are taken into account
+        auto rounds = [&](auto tied) {   // until a round finds no candidates or too many: their number
+            constexpr bool TIED = decltype(tied)::value;
+          for (;;) {
+            update();
+            int most = dm[0];
+#pragma unroll
+            for (int q = 1; q < P; ++q) most = max(most, dm[q]);
+            auto collect = [&](auto above_it) {
+#pragma unroll
+                for (int q = 0; q < P; ++q) {
+                    if (above_it(q)) {
+                        const int slot = atomicAdd(&s_cnt[now], 1);
+                        if (slot < KEEP) {
+                            s_ent[par][slot] = make_float4(px[q], py[q], pz[q], __int_as_float(dm[q]));
+                            s_eix[par][slot] = ~index(q);
+                        }
+                    }
+                }
+            };
+            if constexpr (!TIED) {
+                if (most > tau) collect([&](int q) { return dm[q] > tau; });
+            } else {
+                collect([&](int q) { return (dm[q] > tau) | ((dm[q] == tau) & (index(q) < tidx)); });
+            }
+            __syncthreads();
+            int n = s_cnt[now];
+            const float4* ent = s_ent[par];
+            const int* eix = s_eix[par];
+            int* lows = s_low[par];
+            float4 e = ent[i];
+            int ei = eix[i];   // the index's complement: larger is earlier
+            constexpr int R = CAP / 2 / W;
+            float4 f[R];
+            int fi[R];
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                f[r] = ent[2 * (wave + r * W) + (lane >> 5)];
+                fi[r] = eix[2 * (wave + r * W) + (lane >> 5)];
+            }
+            n = __builtin_amdgcn_readfirstlane(n);
+            next_round();
+            int bound = tau, above = tau;   // every other point is at most `bound`, or at `above` with a higher index
+            if constexpr (TIED) {
+                bound = tau - 1;
+            } else {
+                step += (step >> 6) * (22 - min(n, 54));
+                step = min(max(step, 1 << 8), 1 << 22);
+            }
+            if (n > CAP && n <= KEEP) {
+                // the largest CAP or fewer: raise the threshold, halving the
+                // interval up to the largest value, then that of the indices
+                // that hold it
+                const float4 g = ent[lane];
+                const int v = lane < n ? __float_as_int(g.w) : INT32_MIN, vi = eix[lane];
+                const int vmax = wave_max_i32(v);
+                uint64_t in = 0;
+                int lo = bound, hi = vmax;
+                while (hi - lo > 1) {
+                    const int mid = lo + (hi - lo) / 2;
+                    const uint64_t t = __builtin_amdgcn_ballot_w64(v > mid);
+                    if (t == 0) hi = mid;
+                    else lo = mid;
+                    if (t != 0 && __builtin_popcountll(t) <= CAP) {
+                        in = t;
+                        break;
+                    }
+                }
+                bound = above = lo;
+                if (in == 0) {
+                    // more than CAP hold the largest value: the lowest indices
+                    bound = vmax - 1;
+                    above = vmax;
+                    lo = -65536;
+                    hi = 1;
+                    for (int it = 0; it < 32 && in == 0; ++it) {
+                        const int mid = lo + (hi - lo) / 2;
+                        const uint64_t t = __builtin_amdgcn_ballot_w64((v == vmax) & (vi + 1 >= mid));
+                        if (t == 0) hi = mid;
+                        else lo = mid;
+                        if (t != 0 && __builtin_popcountll(t) <= CAP) in = t;
+                    }
+                }
+                n = __builtin_popcountll(in);
+                if ((in >> lane) & 1) {   // every wave writes the same
+                    s_list[mask_rank(in)] = g;
+                    s_lidx[mask_rank(in)] = vi;
+                }
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                e = s_list[i];
+                ei = s_lidx[i];
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    f[r] = s_list[2 * (wave + r * W) + (lane >> 5)];
+                    fi[r] = s_lidx[2 * (wave + r * W) + (lane >> 5)];
+                }
+            }
+            if (n == 0 || n > CAP) return n;
+            // half a wave compares candidate j with every candidate i
+            const uint64_t ki = ((uint64_t)__float_as_uint(e.w) << 32) | (uint32_t)ei;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const int j0 = 2 * (wave + r * W);
+                if (j0 < n) {
+                    const uint64_t kj = ((uint64_t)__float_as_uint(f[r].w) << 32) | (uint32_t)fi[r];
+                    const float d = dist3(f[r].x, f[r].y, f[r].z, e.x, e.y, e.z);
+                    const bool ahead = (ki > kj) & (i < n);
+                    const bool lowers = ahead & (d < f[r].w);
+                    const uint64_t am = __builtin_amdgcn_ballot_w64(ahead);
+                    const uint64_t lm = __builtin_amdgcn_ballot_w64(lowers);
+                    if (lowers) atomicMin(&lows[j0 + (lane >> 5)], __float_as_int(d));
+                    if (i == 0)
+                        s_pair[j0 + (lane >> 5)] =
+                            lane ? make_int2((int)(am >> 32), (int)(lm >> 32)) : make_int2((int)am, (int)lm);
+                }
+            }
+            __syncthreads();
+            const int2 pr = s_pair[i];
+            const int low = lows[i];
+            const unsigned ahead = (unsigned)pr.x, lowers = (unsigned)pr.y;
+            const bool real = i < n;
+            const bool lowered = real & (lowers != 0);
+            const unsigned hurt = (unsigned)__builtin_amdgcn_ballot_w64(lowered);
+            int val = (lowers & hurt) != 0 ? __float_as_int(e.w) : low;
+            val = lowered ? val : 0;
+            const int up = row_max_i32(val);
+            const int upmax = max(__builtin_amdgcn_readlane(up, 0), __builtin_amdgcn_readlane(up, 16));
+            bound = max(bound, upmax);
+            above = max(above, upmax);
+            valid = real & !lowered & ((ahead == 0) | (__float_as_int(e.w) > bound));
+            place = __builtin_popcount(ahead & ~hurt);
+            c = min(__builtin_popcount((unsigned)__builtin_amdgcn_ballot_w64(valid)), M - m);
+            s = make_float4(e.x, e.y, e.z, __int_as_float(~ei));
+            dmax = top;
+            top = above;
+            record();
+            if (m >= M) return 0;
+            if constexpr (TIED) {
+                tidx += tinc;
+            } else {
+                tau = max(above - step, 0);
+            }
+          }
+        };
+        const int n = tidx == 0 ? rounds(std::false_type()) : rounds(std::true_type());
+        if (m >= M) break;
+        // no candidate, or more than are kept: select the maximum next, then
+        // in the latter case (most often many equal values) as many of the
+        // points that equal it as are wanted, by index
+        valid = false;
+        c = 0;
+        single = m + 1;
+        if (n > 0) {
+            tinc = max(1, (tidx > 0 ? tinc : N) * 22 / n);
+            level = -1;
+        } else {
+            tinc = min(2 * tinc, N);
+            if (tidx == 0) top = tau;
+        }
+    }
+    if constexpr (!XY) {
+        __syncthreads();
+        for (int o = tid; o < M; o += T) {
+            const int j = s_out[o];
+            out_idx[o] = j;
+            if (out_c) {
+                out_c[3 * o + 0] = s_c[3 * j + 0];
+                out_c[3 * o + 1] = s_c[3 * j + 1];
+                out_c[3 * o + 2] = s_c[3 * j + 2];
+            }
+        }
+    }
+}
+
+template <int T, int P, int RG>
+static void launch_fps_rounds(const float* xyz, int64_t B, int N, int M, int32_t* idx, float* cxyz, hipStream_t s) {
+    fps_rounds_kernel<T, P, RG><<<dim3((unsigned)B), dim3(T), 0, s>>>(xyz, N, M, idx, cxyz);
+}
+
 template <int T, int P, bool REG>
 static void launch_fps(const float* xyz, int64_t B, int N, int M, int32_t* idx, float* cxyz, hipStream_t s) {
     fps_kernel<T, P, REG><<<dim3((unsigned)B), dim3(T), 0, s>>>(xyz, N, M, idx, cxyz);
@@ -969,6 +1557,22 @@ extern "C" int mesorasi_fps(const float* xyz, int64_t B, int64_t N, int64_t M, i
         if (pl.P == 4) return launch_fps_multi<4>(xyz, B, n, m, pl.G, idx, cxyz, ws, s);
         if (pl.P == 8) return launch_fps_multi<8>(xyz, B, n, m, pl.G, idx, cxyz, ws, s);
         return launch_fps_multi<16>(xyz, B, n, m, pl.G, idx, cxyz, ws, s);
+    }
+    // From 128 samples on, several per round: below, the spatial sort (5 us at
+    // 1024 points, 20 us at 16384) and the first samples, selected one at a
+    // time (0.6 to 1 us each), are not won back (96 / 128 samples, here against
+    // below: 500 points 30.2 / 33.8 against 29.2 / 38.2 us, 1024 36.5 / 39.9
+    // against 31.7 / 41.3, 4096 59.9 / 65.5 against 50.6 / 65.2, 16384 123 /
+    // 141 against 116 / 143).  Up to 256 points one wave without barriers is
+    // as fast (250 points, 125 samples: 28 against 32 us).
+    if (n > 256 && n <= 16384 && m >= 128) {
+        if (n <= 512) launch_fps_rounds<512, 1, 1>(xyz, B, n, m, idx, cxyz, s);
+        else if (n <= 1024) launch_fps_rounds<512, 2, 2>(xyz, B, n, m, idx, cxyz, s);
+        else if (n <= 2048) launch_fps_rounds<1024, 2, 2>(xyz, B, n, m, idx, cxyz, s);
+        else if (n <= 4096) launch_fps_rounds<1024, 4, 2>(xyz, B, n, m, idx, cxyz, s);
+        else if (n <= 8192) launch_fps_rounds<1024, 8, 4>(xyz, B, n, m, idx, cxyz, s);
+        else launch_fps_rounds<1024, 16, 8>(xyz, B, n, m, idx, cxyz, s);
+        return after_launch("mesorasi_fps");
     }
     // workgroup shape per cloud size, from a sweep on MI355X: the iteration
     // time is a fixed reduction/barrier chain plus P points of VALU work

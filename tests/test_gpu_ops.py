@@ -79,6 +79,19 @@ FPS_CASES = [
     ("skip_mesh", 2, 16384, 3000, "mesh"),
     ("skip_far_outlier", 1, 12000, 500, "outlier"),    # one point 1e6 away: a coarse grid
     ("lidar_sa1", 1, 16384, 4096, "lidar"),
+    # 257 .. 16384 points and 128 samples or more: several samples per round
+    ("rounds_257", 3, 257, 257, "normal"),             # the smallest cloud; every point
+    ("rounds_512_grid", 2, 512, 512, "grid"),          # 64 distinct points: equal maxima, then zeros
+    ("rounds_513", 2, 513, 128, "mesh"),               # one point in the last row; the fewest samples
+    ("rounds_1024_lattice", 2, 1024, 700, "lattice"),  # distinct points, nearly all maxima equal
+    ("rounds_1025_flat", 2, 1025, 600, "flat"),        # one axis constant
+    ("rounds_2048_line", 2, 2048, 300, "line"),        # two axes constant
+    ("rounds_2049_same", 1, 2049, 200, "same"),        # one point repeated
+    ("rounds_4096_lattice", 1, 4096, 1024, "lattice"),
+    ("rounds_4097_outlier", 2, 4097, 1000, "outlier"),  # one slab holds nearly every bin's points
+    ("rounds_8192_cube", 2, 8192, 1500, "cube"),
+    ("rounds_8193_m_eq_n", 1, 8193, 8193, "mesh"),
+    ("rounds_16384_lattice", 1, 16384, 2000, "lattice"),
     ("n20000", 1, 20000, 64, "normal"),
     ("n32768_global_path", 1, 32768, 40, "normal"),   # coordinates re-read from memory per iteration
     ("n_max", 1, 65536, 24, "normal"),                # the documented maximum cloud size
@@ -99,6 +112,13 @@ def _points(kind, B, N, r):
     if kind == "dups":
         base = r.standard_normal((B, N // 4, 3)).astype(np.float32)
         return base[:, r.integers(0, N // 4, N)]
+    if kind == "lattice":   # distinct points of a 32 x 32 x 16 lattice, shuffled
+        c = np.stack(np.meshgrid(np.arange(32), np.arange(32), np.arange(16), indexing="ij"), -1).reshape(-1, 3)
+        return np.stack([c[np.sort(r.permutation(len(c))[:N])][r.permutation(N)] for _ in range(B)]).astype(np.float32)
+    if kind in ("flat", "line"):
+        x = r.standard_normal((B, N, 3)).astype(np.float32)
+        x[..., 1 if kind == "line" else 2:] = 0.25
+        return x
     if kind == "cube":
         return synth.uniform_cube(r, B, N)
     if kind == "mesh":

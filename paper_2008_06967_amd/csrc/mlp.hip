@@ -912,15 +912,25 @@ static bool use_fused(int64_t rows, int n_layers, const int32_t* dims, int dtype
 // and HBM round trips dominate (65536 x 3 -> 32 -> 32 -> 64: 16.6 against
 // 20.8 us); on 128-wide rows the bf16 GEMM is faster (65536 x 128 -> 128
 // -> 128: 28.5 against 34.7 us), its MFMA work being a sixteenth of fp32's.
-#ifndef MESO_RR_MIN_ROWS
-#define MESO_RR_MIN_ROWS (kFusedMaxPlainRows + 1)
-#endif
-static bool use_rr(int64_t rows, int n_layers, const int32_t* dims, int dtype, int out_dtype, int64_t pool_group,
+// A first layer of a wide and a narrow source (65536 x 131 -> 128 -> 128 ->
+// 128) takes it too: 80 us against 100 for the GEMM layers.
+constexpr int64_t kRrMinRows = kFusedMaxPlainRows + 1;
+static bool use_rr(const float* x0, int c0, int64_t ld0, const float* x1, int c1, int64_t ld1, int64_t rows,
+                   int n_layers, const int32_t* dims, int dtype, int out_dtype, int64_t pool_group,
                    bool neighbor_rows) {
-    if (pool_group != 0 || neighbor_rows || rows < MESO_RR_MIN_ROWS) return false;
-    if (dtype == MESORASI_F32) return out_dtype == MESORASI_F32 && rr_mlp_supported(n_layers, dims, rows);
+    if (pool_group != 0 || neighbor_rows || rows < kRrMinRows) return false;
+    if (dtype == MESORASI_F32)
+        return out_dtype == MESORASI_F32 && rr_mlp_supported(x0, c0, ld0, x1, c1, ld1, n_layers, dims, rows);
     return dtype == MESORASI_BF16 && dims[0] <= 32 && rb_mlp_supported(n_layers, dims);
 }
+
+// Gathered neighbor rows pooled over 16 or 32 of them take the register MLP
+// from this count on, one tile per wave of a chip's persistent workgroups
+// (3 -> 64 -> 64 -> 128: 65536 rows 26 against 38 us fused, 524288 rows 144
+// against 217 with 32 per centroid and 75 against 300 with 16, whose atomic
+// max per half tile is what the fused kernel spends its time on); with fewer
+// rows, waves stay empty and the fused kernel is as fast.
+constexpr int64_t kRrMinPooledRows = 65536;
 
 static size_t mlp_ws_bytes(int64_t rows, int n_layers, const int32_t* dims, int dtype, bool neighbor_rows) {
     if (use_fused(rows, n_layers, dims, dtype, neighbor_rows)) return 0;
@@ -1049,7 +1059,11 @@ static int run_mlp(const float* x0, int c0, int64_t ld0, const float* x1, int c1
                    int n_layers, const int32_t* dims, const void* const* W, const float* const* bias,
                    uint32_t relu_mask, int dtype, int out_dtype, void* y, int64_t ld_y, int64_t pool_group, void* ws,
                    hipStream_t s, bool neighbor_rows, const MlpGather* g = nullptr) {
-    if (!g && use_rr(rows, n_layers, dims, dtype, out_dtype, pool_group, neighbor_rows)) {
+    if (g && !g->q && dtype == MESORASI_F32 && rows >= kRrMinPooledRows &&
+        rr_pool_supported(c1, x1, ld1, n_layers, dims, g->k))
+        return run_rr_mlp(x0, c0, ld0, x1, c1, ld1, rows, n_layers, dims, W, bias, relu_mask, static_cast<float*>(y),
+                          ld_y, s, nullptr, g);
+    if (!g && use_rr(x0, c0, ld0, x1, c1, ld1, rows, n_layers, dims, dtype, out_dtype, pool_group, neighbor_rows)) {
         if (dtype == MESORASI_BF16)
             return run_rb_mlp(x0, c0, ld0, x1, c1, ld1, rows, n_layers, dims, W, bias, relu_mask, out_dtype, y, ld_y,
                               s);

@@ -51,8 +51,15 @@ int run_fused_mlp(const float* x0, int c0, int64_t ld0, const float* x1, int c1,
 // True when every layer is at most 128 wide (the register-resident MLP,
 // mlp_rr.hip) and either the permuted weights of all layers fit the LDS of
 // one workgroup, or each fits and the rows make at most one 32-row tile
-// per wave (the weights are then staged in phases).
+// per wave (the weights are then staged in phases).  The second form knows
+// the first layer's sources: one of at most 8 channels beside an aligned
+// one of whole 4-channel chunks adds to the 128.
 bool rr_mlp_supported(int n_layers, const int32_t* dims, int64_t rows);
+bool rr_mlp_supported(const float* x0, int c0, int64_t ld0, const float* x1, int c1, int64_t ld1, int n_layers,
+                      const int32_t* dims, int64_t rows);
+
+// The same for gathered neighbor rows pooled over K = 16 or 32 of them.
+bool rr_pool_supported(int cf, const float* feat, int64_t ld_f, int n_layers, const int32_t* dims, int K);
 
 // First-layer rows made by interpolation (mesorasi_interpolate3_mlp): row r
 // = b nd + i is phi(sum_k u_k g[b, nit[r, k]] + add[r]); every row and
@@ -68,10 +75,12 @@ struct RrInterp {
 };
 
 // The register-resident MLP: fp32 rows [x0 | x1] (or interpolated rows) in,
-// fp32 y out, no workspace, no pooling.
+// fp32 y out, no workspace.  With g (q null) the rows are gathered and y
+// takes their max per centroid (every last-layer value not negative).
 int run_rr_mlp(const float* x0, int c0, int64_t ld0, const float* x1, int c1, int64_t ld1, int64_t rows,
                int n_layers, const int32_t* dims, const void* const* W, const float* const* bias,
-               uint32_t relu_mask, float* y, int64_t ld_y, hipStream_t s, const RrInterp* ip = nullptr);
+               uint32_t relu_mask, float* y, int64_t ld_y, hipStream_t s, const RrInterp* ip = nullptr,
+               const MlpGather* g = nullptr);
 
 // The same for bf16 MLPs (mlp_rr_bf16.hip): every layer at most 128 wide;
 // fp32 rows in, fp32 or bf16 y out (bf16-rounded values either way).

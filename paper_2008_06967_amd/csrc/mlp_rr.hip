@@ -20,7 +20,16 @@
 // order, are the only LDS data: a workgroup is persistent, loads every
 // layer's weights and biases once, and its eight waves then stream tiles.
 // The first layer reads its rows straight from memory, the two lanes of a
-// row taking alternate 4-channel chunks.
+// row taking alternate 4-channel chunks.  Its input may have two parts: a
+// wide source of whole aligned 4-channel chunks, and a narrow one of at most
+// 8 channels (the xyz of a module's first layer, the skip features of the
+// finest propagation level), which makes one more group of four k steps.
+//
+// Neighbor rows [xyz_j - cxyz_c | feat_j] of the conventional module are
+// gathered by the same loader, and the max over a centroid's K rows is taken
+// in registers: with K = 32 a tile is one centroid, with K = 16 two, and a
+// lane's accumulators are reduced over the lanes of its half wave (16), so
+// the rows' outputs are neither stored nor cleared beforehand.
 #include <algorithm>
 
 #include "common.h"
@@ -60,9 +69,17 @@ struct RrArgs {
     uint32_t relu_mask;
     float* y;
     int64_t ldy;
-    int k0h;     // layer-0 k values per lane half (a multiple of 16, at most 64)
-    int vec0;    // layer-0 rows read as aligned float4 (one source, C0 % 4 == 0)
+    int k0h;     // layer-0 k values per lane half of the wide source (a multiple of 16, at most 64)
+    int vec0;    // wide layer-0 rows read as aligned float4
+    int cs;      // channels of the narrow source (0: none), at weight column sw; the wide source's are at ww
+    int sw, ww;
+    const float* xs;
+    int64_t lds;
+    int cs0;     // of them the first cs0 from xs, the others from xs1
+    const float* xs1;
+    int64_t lds1;
     int vecy;    // output rows stored as aligned float4
+    MlpGather g; // neighbor rows (xs, x0 = xyz, feat), pooled over g.k
     // interpolated first-layer rows (instead of [x0 | x1]): row r = b Nd + i
     // is phi(sum_k u_k g[b, nn[r, k]] + add[r]) over the first dims[0]
     // channels, u_k the normalised inverse squared distances
@@ -72,9 +89,10 @@ struct RrArgs {
 
 __host__ __device__ inline int rr_blocks(int n) { return (n + 31) / 32; }
 // k steps of layer l: 16 per 32-channel input block; the first layer's
-// half-rows are padded to whole blocks of 16 steps too (k0h = 16 nj)
-__host__ __device__ inline int rr_steps(const int* dims, int l, int k0h) {
-    return l == 0 ? k0h : 16 * rr_blocks(dims[l]);
+// half-rows are padded to whole blocks of 16 steps too (k0h = 16 nj), and its
+// narrow source takes 4 ahead of them
+__host__ __device__ inline int rr_steps(const int* dims, int l, int k0h, int cs) {
+    return l == 0 ? k0h + (cs > 0 ? 4 : 0) : 16 * rr_blocks(dims[l]);
 }
 
 // The input channel that lane half h supplies at k step s of layer l.
@@ -86,25 +104,22 @@ __device__ __forceinline__ int rr_k(int l, int s, int h) {
     return 32 * j + 8 * (r >> 2) + (r & 3) + 4 * h;
 }
 
-// One layer's products: NJ input blocks of 16 k steps, NOB output blocks,
-// the output blocks' accumulation chains interleaved step by step.
+// One layer's products: NJ input blocks of 16 k steps, NOB output blocks
+// whose weights lie `ng` groups of four steps apart, the output blocks'
+// accumulation chains interleaved step by step.
 template <int NJ, int NOB>
-__device__ __forceinline__ void rr_products(const float4* __restrict__ wl, const float (&act)[kRrMaxSteps],
+__device__ __forceinline__ void rr_products(const float4* __restrict__ wl, int ng, const float (&act)[kRrMaxSteps],
                                             f32x16 (&acc)[kRrMaxWidth / 32]) {
-#pragma unroll
-    for (int ob = 0; ob < NOB; ++ob)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[ob][r] = 0.0f;
     float4 w[NOB];
 #pragma unroll
-    for (int ob = 0; ob < NOB; ++ob) w[ob] = wl[ob * 4 * NJ * 64];
+    for (int ob = 0; ob < NOB; ++ob) w[ob] = wl[ob * ng * 64];
 #pragma unroll
     for (int g = 0; g < 4 * NJ; ++g) {
         // the next group's weights are requested before this group's MFMAs
         float4 wn[NOB];
         if (g + 1 < 4 * NJ) {
 #pragma unroll
-            for (int ob = 0; ob < NOB; ++ob) wn[ob] = wl[(ob * 4 * NJ + g + 1) * 64];
+            for (int ob = 0; ob < NOB; ++ob) wn[ob] = wl[(ob * ng + g + 1) * 64];
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -129,22 +144,45 @@ __device__ __forceinline__ void rr_products(const float4* __restrict__ wl, const
 }
 
 template <int NJ>
-__device__ __forceinline__ void rr_products_nob(int nob, const float4* __restrict__ wl,
+__device__ __forceinline__ void rr_products_nob(int nob, const float4* __restrict__ wl, int ng,
                                                 const float (&act)[kRrMaxSteps], f32x16 (&acc)[kRrMaxWidth / 32]) {
     switch (nob) {
-        case 1: rr_products<NJ, 1>(wl, act, acc); break;
-        case 2: rr_products<NJ, 2>(wl, act, acc); break;
-        case 3: rr_products<NJ, 3>(wl, act, acc); break;
-        default: rr_products<NJ, 4>(wl, act, acc); break;
+        case 1: rr_products<NJ, 1>(wl, ng, act, acc); break;
+        case 2: rr_products<NJ, 2>(wl, ng, act, acc); break;
+        case 3: rr_products<NJ, 3>(wl, ng, act, acc); break;
+        default: rr_products<NJ, 4>(wl, ng, act, acc); break;
     }
+}
+
+// The narrow source's four steps.
+__device__ __forceinline__ void rr_narrow(int nob, const float4* __restrict__ wl, int ng, const float (&sm)[4],
+                                          f32x16 (&acc)[kRrMaxWidth / 32]) {
+#pragma unroll
+    for (int ob = 0; ob < kRrMaxWidth / 32; ++ob) {
+        if (ob < nob) {
+            const float4 w = wl[ob * ng * 64];
+            acc[ob] = __builtin_amdgcn_mfma_f32_32x32x2f32(w.x, sm[0], acc[ob], 0, 0, 0);
+            acc[ob] = __builtin_amdgcn_mfma_f32_32x32x2f32(w.y, sm[1], acc[ob], 0, 0, 0);
+            acc[ob] = __builtin_amdgcn_mfma_f32_32x32x2f32(w.z, sm[2], acc[ob], 0, 0, 0);
+            acc[ob] = __builtin_amdgcn_mfma_f32_32x32x2f32(w.w, sm[3], acc[ob], 0, 0, 0);
+        }
+    }
+}
+
+// ReLU in one instruction (a NaN gives 0, as a comparison with 0 does).
+__device__ __forceinline__ float rr_relu(float v) {
+    float r;
+    asm("v_max_f32 %0, 0, %1" : "=v"(r) : "v"(v));
+    return r;
 }
 
 // Eight waves, two per SIMD: while one wave waits on its rows or runs its
 // epilogue, the other keeps the SIMD's MFMA pipe busy.  (A four-wave form
 // with 512 registers per wave that requested its next tile's rows before
 // computing the current one measured 9-18 % slower.)
-// PHASED: the weights staged in phases, at most one tile per wave.
-template <bool PHASED>
+// PHASED: the weights staged in phases, at most one tile per wave.  POOLED:
+// gathered neighbor rows, the output their max per centroid.
+template <bool PHASED, bool POOLED>
 __global__ __launch_bounds__(64 * kRrWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void mlp_rr_kernel(RrArgs a) {
     extern __shared__ float4 smem4[];
@@ -152,7 +190,7 @@ void mlp_rr_kernel(RrArgs a) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int hk = lane >> 5;
 
-    float act[kRrMaxSteps];
+    float act[kRrMaxSteps], sm[4];
     // layer-0 input of tile t: this lane's row; step s takes channel
     // 8 (s / 4) + 4 hk + s % 4
     auto load_tile = [&](int64_t t, float (&dst)[kRrMaxSteps]) {
@@ -163,6 +201,42 @@ void mlp_rr_kernel(RrArgs a) {
         // some hundred registers for its whole length)
         int kb = 4 * hk;
         asm volatile("" : "+v"(kb));
+        if constexpr (POOLED) {
+            const int64_t r0 = rok ? row : 0;
+            const int64_t cloud = (int64_t)((uint64_t)r0 / (uint64_t)a.g.mk);
+            const int64_t j = cloud * a.g.n + a.g.nit[r0];
+            const float* pj = a.xs + j * 3;
+            const float* pc = a.g.cxyz + (int64_t)((uint64_t)r0 / (uint32_t)a.g.k) * 3;
+            const bool ok = rok && hk == 0;
+            sm[0] = ok ? pj[0] - pc[0] : 0.0f;
+            sm[1] = ok ? pj[1] - pc[1] : 0.0f;
+            sm[2] = ok ? pj[2] - pc[2] : 0.0f;
+            sm[3] = 0.0f;
+            const float* src = a.x0 + j * a.ld0;
+#pragma unroll
+            for (int i = 0; i < kRrMaxSteps / 4; ++i) {
+                if (4 * i < a.k0h) {
+                    const int k = kb + 8 * i;
+                    const bool in = rok && k < a.c0;
+                    const float4 v = *reinterpret_cast<const float4*>(src + (in ? k : 0));
+                    dst[4 * i + 0] = in ? v.x : 0.0f;
+                    dst[4 * i + 1] = in ? v.y : 0.0f;
+                    dst[4 * i + 2] = in ? v.z : 0.0f;
+                    dst[4 * i + 3] = in ? v.w : 0.0f;
+                }
+            }
+            return;
+        }
+        if (a.cs > 0) {
+            const float* xr = a.xs + (rok ? row : 0) * a.lds;
+            const float* xq = a.cs0 < a.cs ? a.xs1 + (rok ? row : 0) * a.lds1 - a.cs0 : xr;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int k = 4 * hk + e;
+                const float v = k < a.cs0 || k >= a.cs ? xr[k < a.cs0 ? k : 0] : xq[k];
+                sm[e] = rok && k < a.cs ? v : 0.0f;
+            }
+        }
         if (a.interp) {
             // the interpolation of mesorasi_interpolate3_add, in its fp32
             // operations, then the addition and phi
@@ -242,21 +316,22 @@ void mlp_rr_kernel(RrArgs a) {
     // contiguous range of tiles -- whole clouds -- and keep those gathers in
     // its own L2
     int64_t wg = blockIdx.x;
-    if (a.interp && (gridDim.x & 7) == 0) wg = (int64_t)(blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    if ((POOLED || a.interp) && (gridDim.x & 7) == 0)
+        wg = (int64_t)(blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
     const int64_t t0 = wg * kRrWaves + wave;
     if (t0 < a.tiles) load_tile(t0, act);
 
     // weights: layer l, output block ob, step group g = s / 4, lane, s % 4;
-    // thread tid fills float4s tid + 512 u (u < 8: at most 4 blocks x 16
+    // thread tid fills float4s tid + 512 u (at most 4 blocks x 17
     // groups x 64 lanes), each 4 consecutive k of one weight row; all of a
     // layer's loads are in flight before the first LDS store
-    constexpr int kPer = 4 * 16 * 64 / (64 * kRrWaves);
+    constexpr int kPer = (4 * 17 * 64 + 64 * kRrWaves - 1) / (64 * kRrWaves);
     auto stage = [&](int l0, int l1) {
         for (int l = l0; l < l1; ++l) {
             const int K = a.dims[l], N = a.dims[l + 1];
-            const int ng = rr_steps(a.dims, l, a.k0h) / 4;
+            const int ng = rr_steps(a.dims, l, a.k0h, a.cs) / 4;
             const int total = rr_blocks(N) * ng * 64;
-            const unsigned inv = (65536u + ng - 1) / ng;   // gg / ng exactly for gg < 64
+            const unsigned inv = (65536u + ng - 1) / ng;   // gg / ng exactly for gg < 128
             const float* __restrict__ W = a.W[l];
             const bool wvec = (K % 4) == 0 && (reinterpret_cast<uintptr_t>(W) & 15) == 0;
             float4 v[kPer];
@@ -266,17 +341,22 @@ void mlp_rr_kernel(RrArgs a) {
                 const int ln = i & 63, gg = i >> 6;
                 const int ob = (int)(((unsigned)gg * inv) >> 16), g = gg - ob * ng;
                 const int n = ob * 32 + (ln & 31);
-                const int k = rr_k(l, 4 * g, ln >> 5);   // k .. k + 3 are consecutive
+                // columns k .. k + 3 of [base, end): a layer's inputs, or one
+                // of the first layer's two sources
+                const bool two = l == 0 && a.cs > 0, narrow = two && g == 0;
+                const int base = two ? (narrow ? a.sw : a.ww) : 0;
+                const int end = two ? base + (narrow ? a.cs : K - a.cs) : K;
+                const int k = base + (narrow ? 4 * (ln >> 5) : rr_k(l, 4 * (two ? g - 1 : g), ln >> 5));
                 v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
                 if (i < total && n < N) {
                     const float* wr = W + (int64_t)n * K;
-                    if (wvec && k + 4 <= K) {
+                    if (wvec && !two && k + 4 <= K) {
                         v[u] = *reinterpret_cast<const float4*>(wr + k);
                     } else {
-                        v[u].x = k + 0 < K ? wr[k + 0] : 0.0f;
-                        v[u].y = k + 1 < K ? wr[k + 1] : 0.0f;
-                        v[u].z = k + 2 < K ? wr[k + 2] : 0.0f;
-                        v[u].w = k + 3 < K ? wr[k + 3] : 0.0f;
+                        v[u].x = k + 0 < end ? wr[k + 0] : 0.0f;
+                        v[u].y = k + 1 < end ? wr[k + 1] : 0.0f;
+                        v[u].z = k + 2 < end ? wr[k + 2] : 0.0f;
+                        v[u].w = k + 3 < end ? wr[k + 3] : 0.0f;
                     }
                 }
             }
@@ -297,33 +377,95 @@ void mlp_rr_kernel(RrArgs a) {
     auto layer = [&](int l, int64_t row, bool rok) {
         const int N = a.dims[l + 1];
         const int nob = rr_blocks(N);
-        const int nj = rr_steps(a.dims, l, a.k0h) / 16;
+        const int ng = rr_steps(a.dims, l, a.k0h, a.cs) / 4;
         const float4* __restrict__ wl = smem4 + (a.woff[l] >> 2) + lane;
         f32x16 acc[kRrMaxWidth / 32];
-        switch (nj) {
-            case 1: rr_products_nob<1>(nob, wl, act, acc); break;
-            case 2: rr_products_nob<2>(nob, wl, act, acc); break;
-            case 3: rr_products_nob<3>(nob, wl, act, acc); break;
-            default: rr_products_nob<4>(nob, wl, act, acc); break;
-        }
         const bool relu = (a.relu_mask >> l) & 1u;
-        const float* __restrict__ bl = smem + a.boff[l];
+        // the sums start from the bias: VALU work that does not overlap the
+        // MFMAs is what this kernel loses
+        const float* __restrict__ bl = smem + a.boff[l] + 4 * hk;
+#pragma unroll
+        for (int ob = 0; ob < kRrMaxWidth / 32; ++ob) {
+            if (ob < nob) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const float4 b4 = *reinterpret_cast<const float4*>(bl + 32 * ob + 8 * q);
+                    acc[ob][4 * q + 0] = b4.x;
+                    acc[ob][4 * q + 1] = b4.y;
+                    acc[ob][4 * q + 2] = b4.z;
+                    acc[ob][4 * q + 3] = b4.w;
+                }
+            }
+        }
+        if (l == 0 && a.cs > 0) {
+            rr_narrow(nob, wl, ng, sm, acc);
+            wl += 64;
+        }
+        switch (ng >> 2) {   // (the narrow source's group is the odd one)
+            case 0: break;
+            case 1: rr_products_nob<1>(nob, wl, ng, act, acc); break;
+            case 2: rr_products_nob<2>(nob, wl, ng, act, acc); break;
+            case 3: rr_products_nob<3>(nob, wl, ng, act, acc); break;
+            default: rr_products_nob<4>(nob, wl, ng, act, acc); break;
+        }
         if (l + 1 < a.n_layers) {
-            // bias and activation in place: the accumulators become the
-            // next layer's B operand in its k order (steps past the
-            // layer's blocks are never read)
+            // the accumulators, activated, become the next layer's B operand
+            // in its k order (steps past the layer's blocks are never read)
 #pragma unroll
             for (int ob = 0; ob < kRrMaxWidth / 32; ++ob) {
                 if (ob < nob) {
+                    if (relu) {
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) act[16 * ob + r] = rr_relu(acc[ob][r]);
+                    } else {
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) act[16 * ob + r] = acc[ob][r];
+                    }
+                }
+            }
+        } else if constexpr (POOLED) {
+            // the max over the 16 or 32 lanes that hold a centroid's rows
+            // (the values are not negative: they order as their bits); the
+            // last quad of the group stores it
+            const bool whole = a.g.k == 32;
+            const bool last = rok && (lane & (whole ? 28 : 12)) == (whole ? 28 : 12);
+            float* yr = a.y + (int64_t)((uint64_t)row / (uint32_t)a.g.k) * a.ldy;
+            const bool odd = lane & 1, high = lane & 2;
+#pragma unroll
+            for (int ob = 0; ob < kRrMaxWidth / 32; ++ob) {
+                if (ob < nob) {
+                    // quads first, halving the registers: lane i of a quad
+                    // ends with the quad's max of channel i of each four
+                    int m[4];
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
-                        const float4 b4 = *reinterpret_cast<const float4*>(bl + 32 * ob + 8 * q + 4 * hk);
-                        const float bq[4] = {b4.x, b4.y, b4.z, b4.w};
+                        int v[4], h[2];
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            float v = acc[ob][4 * q + i] + bq[i];
-                            if (relu) v = v > 0.0f ? v : 0.0f;
-                            act[16 * ob + 4 * q + i] = v;
+                        for (int i = 0; i < 4; ++i) v[i] = __float_as_int(rr_relu(acc[ob][4 * q + i]));
+#pragma unroll
+                        for (int i = 0; i < 2; ++i) {   // channels 2 i, 2 i + 1: even lanes keep the first
+                            const int give = odd ? v[2 * i] : v[2 * i + 1], keep = odd ? v[2 * i + 1] : v[2 * i];
+                            h[i] = max(keep, __builtin_amdgcn_mov_dpp(give, 0xB1, 0xf, 0xf, true));   // lane ^ 1
+                        }
+                        const int give = high ? h[0] : h[1], keep = high ? h[1] : h[0];
+                        m[q] = max(keep, __builtin_amdgcn_mov_dpp(give, 0x4E, 0xf, 0xf, true));       // lane ^ 2
+                    }
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) m[q] = dpp_max_i32<0x124>(m[q]);   // row_ror:4
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) m[q] = dpp_max_i32<0x128>(m[q]);   // row_ror:8
+                    if (whole) {
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {   // the row above and the row below
+                            auto w = __builtin_amdgcn_permlane16_swap((unsigned)m[q], (unsigned)m[q], false, false);
+                            m[q] = max((int)w[0], (int)w[1]);
+                        }
+                    }
+                    if (last) {
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            const int c = 32 * ob + 8 * q + 4 * hk + (lane & 3);
+                            if (c < N) yr[c] = __int_as_float(m[q]);
                         }
                     }
                 }
@@ -336,12 +478,10 @@ void mlp_rr_kernel(RrArgs a) {
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
                         const int c = 32 * ob + 8 * q + 4 * hk;
-                        const float4 b4 = *reinterpret_cast<const float4*>(bl + c);
-                        float v[4] = {acc[ob][4 * q + 0] + b4.x, acc[ob][4 * q + 1] + b4.y,
-                                      acc[ob][4 * q + 2] + b4.z, acc[ob][4 * q + 3] + b4.w};
+                        float v[4] = {acc[ob][4 * q + 0], acc[ob][4 * q + 1], acc[ob][4 * q + 2], acc[ob][4 * q + 3]};
                         if (relu) {
 #pragma unroll
-                            for (int i = 0; i < 4; ++i) v[i] = v[i] > 0.0f ? v[i] : 0.0f;
+                            for (int i = 0; i < 4; ++i) v[i] = rr_relu(v[i]);
                         }
                         if (a.vecy && c + 4 <= N) {
                             *reinterpret_cast<float4*>(yr + c) = make_float4(v[0], v[1], v[2], v[3]);
@@ -393,25 +533,27 @@ struct RrPlan {
 
 // Layers packed greedily into phases whose permuted weights and biases fit
 // the LDS (one phase when they all fit).
-RrPlan rr_plan(int n_layers, const int32_t* dims) {
+// cs: the channels of dims[0] that come from a narrow source.
+RrPlan rr_plan(int n_layers, const int32_t* dims, int cs) {
     RrPlan p{};
-    p.k0h = (int)(ceil_div(ceil_div(dims[0], 2), 16) * 16);
-    if (p.k0h > kRrMaxSteps || n_layers < 1) return p;
+    if (n_layers < 1 || cs > 8 || cs > dims[0]) return p;
+    p.k0h = (int)(ceil_div(ceil_div(dims[0] - cs, 2), 16) * 16);
+    if (p.k0h > kRrMaxSteps) return p;
     const int cap = kRrMaxLds / (int)sizeof(float);
     int off = 0, most = 0;
     p.nphase = 1;
     p.phase_first[0] = 0;
     for (int l = 0; l < n_layers; ++l) {
-        if (dims[l + 1] > kRrMaxWidth || dims[l] > kRrMaxWidth) return p;
+        if (dims[l + 1] > kRrMaxWidth || (l > 0 && dims[l] > kRrMaxWidth)) return p;
         const int nob = rr_blocks(dims[l + 1]);
-        const int size = nob * rr_steps(dims, l, p.k0h) * 64 + nob * 32;
+        const int size = nob * rr_steps(dims, l, p.k0h, cs) * 64 + nob * 32;
         if (size > cap) return p;
         if (off + size > cap) {
             p.phase_first[p.nphase++] = l;
             off = 0;
         }
         p.woff[l] = off;
-        p.boff[l] = off + nob * rr_steps(dims, l, p.k0h) * 64;
+        p.boff[l] = off + nob * rr_steps(dims, l, p.k0h, cs) * 64;
         off += size;
         most = std::max(most, off);
     }
@@ -432,32 +574,87 @@ int rr_cus() {
 
 }  // namespace
 
+// How a first layer's sources [x0 | x1] are read: which one is narrow (0 or
+// 1; 2: both, -1: neither, the element loader of at most 128 channels).
+static int rr_narrow_source(const float* x0, int c0, int64_t ld0, const float* x1, int c1, int64_t ld1) {
+    const auto wide = [](const float* x, int c, int64_t ld) { return c % 4 == 0 && ld % 4 == 0 && aligned(x, 16); };
+    if (!x1 || c1 == 0) return c0 <= 8 ? 2 : -1;
+    if (c0 + c1 <= 8) return 2;
+    if (c0 <= 8 && wide(x1, c1, ld1)) return 0;
+    if (c1 <= 8 && wide(x0, c0, ld0)) return 1;
+    return -1;
+}
+
 // One phase for any row count; several only while every wave holds at most
 // one 32-row tile (one persistent workgroup of kRrWaves waves per CU).
-bool rr_mlp_supported(int n_layers, const int32_t* dims, int64_t rows) {
-    const RrPlan pl = rr_plan(n_layers, dims);
+static bool rr_rows_ok(const RrPlan& pl, int64_t rows) {
     return pl.ok && (pl.nphase == 1 || ceil_div(rows, 32) <= (int64_t)rr_cus() * kRrWaves);
+}
+
+bool rr_mlp_supported(int n_layers, const int32_t* dims, int64_t rows) {
+    return dims[0] <= kRrMaxWidth && rr_rows_ok(rr_plan(n_layers, dims, 0), rows);
+}
+
+bool rr_mlp_supported(const float* x0, int c0, int64_t ld0, const float* x1, int c1, int64_t ld1, int n_layers,
+                      const int32_t* dims, int64_t rows) {
+    const int narrow = rr_narrow_source(x0, c0, ld0, x1, c1, ld1);
+    if (narrow < 0) return rr_mlp_supported(n_layers, dims, rows);
+    return rr_rows_ok(rr_plan(n_layers, dims, narrow == 2 ? dims[0] : narrow == 0 ? c0 : c1), rows);
+}
+
+bool rr_pool_supported(int cf, const float* feat, int64_t ld_f, int n_layers, const int32_t* dims, int K) {
+    if (K != 16 && K != 32) return false;
+    if (cf > 0 && (cf % 4 != 0 || ld_f % 4 != 0 || !aligned(feat, 16))) return false;
+    const RrPlan pl = rr_plan(n_layers, dims, 3);
+    return pl.ok && pl.nphase == 1;
 }
 
 int run_rr_mlp(const float* x0, int c0, int64_t ld0, const float* x1, int c1, int64_t ld1, int64_t rows,
                int n_layers, const int32_t* dims, const void* const* W, const float* const* bias,
-               uint32_t relu_mask, float* y, int64_t ld_y, hipStream_t s, const RrInterp* ip) {
-    const RrPlan pl = rr_plan(n_layers, dims);
+               uint32_t relu_mask, float* y, int64_t ld_y, hipStream_t s, const RrInterp* ip, const MlpGather* g) {
+    const int narrow = ip ? -1 : g ? 0 : rr_narrow_source(x0, c0, ld0, x1, c1, ld1);
+    const int cs = narrow < 0 ? 0 : narrow == 2 ? dims[0] : narrow == 0 ? c0 : c1;
+    const RrPlan pl = rr_plan(n_layers, dims, cs);
     MESO_REQUIRE(pl.ok, MESORASI_EUNSUPPORTED, "mesorasi_pointwise_mlp: layers too wide for the register MLP");
     if (rows == 0) return MESORASI_OK;
     const int cus = rr_cus();
-    MESO_REQUIRE(pl.nphase == 1 || ceil_div(rows, 32) <= (int64_t)cus * kRrWaves, MESORASI_EUNSUPPORTED,
+    MESO_REQUIRE(rr_rows_ok(pl, rows) && (!g || pl.nphase == 1), MESORASI_EUNSUPPORTED,
                  "mesorasi_pointwise_mlp: staged register MLP on more than one tile per wave");
-    static const hipError_t attr[2] = {
-        hipFuncSetAttribute(reinterpret_cast<const void*>(&mlp_rr_kernel<false>),
+    static const hipError_t attr[3] = {
+        hipFuncSetAttribute(reinterpret_cast<const void*>(&mlp_rr_kernel<false, false>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, kRrMaxLds),
-        hipFuncSetAttribute(reinterpret_cast<const void*>(&mlp_rr_kernel<true>),
+        hipFuncSetAttribute(reinterpret_cast<const void*>(&mlp_rr_kernel<true, false>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, kRrMaxLds),
+        hipFuncSetAttribute(reinterpret_cast<const void*>(&mlp_rr_kernel<false, true>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, kRrMaxLds)};
-    MESO_REQUIRE(attr[0] == hipSuccess && attr[1] == hipSuccess, MESORASI_EHIP,
-                 "mesorasi_pointwise_mlp: LDS size attribute: %s",
-                 hipGetErrorString(attr[0] != hipSuccess ? attr[0] : attr[1]));
+    for (const hipError_t e : attr)
+        MESO_REQUIRE(e == hipSuccess, MESORASI_EHIP, "mesorasi_pointwise_mlp: LDS size attribute: %s",
+                     hipGetErrorString(e));
     RrArgs a{};
     a.x0 = x0; a.ld0 = ld0; a.x1 = x1; a.ld1 = ld1; a.c0 = c0; a.c1 = x1 ? c1 : 0;
+    if (narrow >= 0) {
+        // the narrow source apart, the wide one (if any) alone as x0
+        a.cs = cs;
+        a.xs = narrow == 1 ? x1 : x0;
+        a.lds = narrow == 1 ? ld1 : ld0;
+        a.cs0 = narrow == 2 ? c0 : cs;
+        a.xs1 = narrow == 2 ? a.x1 : nullptr;
+        a.lds1 = ld1;
+        a.sw = narrow == 1 ? c0 : 0;
+        a.ww = narrow == 0 ? c0 : 0;
+        if (narrow == 2) {
+            a.x0 = nullptr;
+            a.c0 = 0;
+        }
+        if (narrow == 0) {
+            a.x0 = a.x1;
+            a.ld0 = a.ld1;
+            a.c0 = a.c1;
+        }
+        a.x1 = nullptr;
+        a.c1 = 0;
+    }
+    if (g) a.g = *g;
     a.rows = rows;
     a.tiles = ceil_div(rows, 32);
     a.n_layers = n_layers;
@@ -475,7 +672,7 @@ int run_rr_mlp(const float* x0, int c0, int64_t ld0, const float* x1, int c1, in
     a.y = y;
     a.ldy = ld_y;
     a.k0h = pl.k0h;
-    a.vec0 = a.c1 == 0 && c0 % 4 == 0 && ld0 % 4 == 0 && aligned(x0, 16);
+    a.vec0 = a.c1 == 0 && a.c0 % 4 == 0 && a.ld0 % 4 == 0 && aligned(a.x0, 16);
     if (ip) {
         a.interp = 1;
         a.ip = *ip;
@@ -487,10 +684,11 @@ int run_rr_mlp(const float* x0, int c0, int64_t ld0, const float* x1, int c1, in
     // interpolated rows: a multiple of 8 workgroups where that stays within
     // the CUs (the kernel then orders tiles by XCD)
     int64_t grid = std::min<int64_t>(ceil_div(a.tiles, kRrWaves), cus);
-    if (a.interp && 8 * ceil_div(grid, 8) <= cus) grid = 8 * ceil_div(grid, 8);
+    if ((a.interp || g) && 8 * ceil_div(grid, 8) <= cus) grid = 8 * ceil_div(grid, 8);
     const size_t lds = (size_t)pl.lds_floats * sizeof(float);
-    if (pl.nphase > 1) mlp_rr_kernel<true><<<dim3((unsigned)grid), dim3(64 * kRrWaves), lds, s>>>(a);
-    else mlp_rr_kernel<false><<<dim3((unsigned)grid), dim3(64 * kRrWaves), lds, s>>>(a);
+    if (g) mlp_rr_kernel<false, true><<<dim3((unsigned)grid), dim3(64 * kRrWaves), lds, s>>>(a);
+    else if (pl.nphase > 1) mlp_rr_kernel<true, false><<<dim3((unsigned)grid), dim3(64 * kRrWaves), lds, s>>>(a);
+    else mlp_rr_kernel<false, false><<<dim3((unsigned)grid), dim3(64 * kRrWaves), lds, s>>>(a);
     return after_launch("mesorasi_pointwise_mlp (register MLP)");
 }
 

@@ -470,6 +470,12 @@ MLP_CASES = [
     ("rr_staged_head", 65536, [128], [128, 128, 128, 13], F32),
     ("rr_staged_ragged", 40001, [128], [128, 128, 128, 128, 36], F32),
     ("staged_too_many_rows", 65600, [128], [128, 128, 128, 13], F32),   # beyond one tile per wave: the GEMMs
+    # a narrow source beside a wide one (or alone) as its own k steps
+    ("rr_narrow_first", 40000, [3, 64], [64, 128], F32),
+    ("rr_narrow_last", 40001, [64, 7], [128, 36], F32),
+    ("rr_narrow_alone", 33000, [8], [32, 16], F32),
+    ("rr_narrow_both", 33003, [5, 3], [33, 9], F32),
+    ("rr_staged_136", 65536, [128, 8], [128, 128, 128], F32),   # the widest first layer, in phases
     ("rr_unaligned_out", 40000, [128], [98], F32),        # 98-float output rows: element stores
     # the bf16 form (v_mfma_f32_32x32x16_bf16, activations packed in
     # registers), used for first layers of at most 32 inputs
@@ -590,6 +596,11 @@ CONV_CASES = {
     "split_strided_k24": (3, 200, 45, 24, 64, [96, 160], F32, 72),
     "nfm_width": (2, 256, 40, 16, 130, [64, 160], F32, 0),
     "bf16": (2, 512, 128, 32, 13, [32, 48], BF16, 0),
+    # 65536 rows and more, 16 or 32 per centroid: pooled in registers
+    "rr_pool_xyz": (4, 600, 520, 32, 0, [64, 64, 128], F32, 0),
+    "rr_pool_k16_half_tile": (9, 600, 457, 16, 0, [33, 20], F32, 0),
+    "rr_pool_feat": (4, 512, 512, 32, 64, [64, 100], F32, 0),
+    "rr_pool_k16_strided": (8, 512, 512, 16, 4, [32, 128], F32, 12),
 }
 
 

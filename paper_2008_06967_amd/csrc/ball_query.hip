@@ -13,6 +13,7 @@
 // bounds the candidates.
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "common.h"
 
@@ -396,6 +397,414 @@ __global__ __launch_bounds__(64 * kGridQWaves) void grid_query_kernel(const floa
     if (cnt && lane == 0) cnt[gq] = n;
 }
 
+// ---------------------------------------------------------------------------
+// Cells in LDS for mid-size clouds and many queries.
+//
+// The walk of ball_query_lds_kernel tests the whole cloud for nearly every
+// query (30 us for 16 x 4096 points and 16384 queries: about 13 VALU
+// instructions for every 64 of 67 million tests).  Here every workgroup first
+// groups its cloud by the cells of the grid form above (same cell rule, hence
+// the same exactness) in its own LDS -- rebuilding it in each workgroup costs
+// less than a launch -- and then tests, for each query, only the points of
+// the 27 cells around it.  The cells' points, the cell ends and the hit
+// bitmaps are all read at LDS latency, and the workgroups number at most one
+// per CU, each serving `per` queries.  A query takes GL lanes: 16 where four
+// bitmaps per wave fit (its nine rows of cells hold some ten points each), a
+// whole wave for the larger clouds.
+// ---------------------------------------------------------------------------
+constexpr int kBqCellWaves = 16;
+constexpr int64_t kBqCellSmallN = 5120;   // 16 lanes per query up to here
+constexpr int64_t kBqCellMinN = 1025;
+constexpr int64_t kBqCellMaxN = 8191;
+// Full walks of at least this many steps in all (about 230 per CU): the cells
+// then cost less than what they save, and balls dense enough to end their
+// walks early are recognised from the box alone (K = 32 unless said: 16 x 4096
+// points, 16384 queries, r = 0.1 walk 34.6 / cells 19.2 us, r = 0.4 19.4 /
+// 18.4; 32 x 1500, 22400 queries 22.7 / 15.8; 4 x 8191, 8192 queries 39.6 /
+// 25.8; 16 x 8000, 32000 queries, K = 64 142 / 72; below, 4 x 4096, 4096
+// queries 13.1 / 16.8).
+constexpr int64_t kBqCellMinSteps = 60000;
+constexpr float kBqDense = 0.7f;          // of the candidates at which one query's walk costs the same
+
+// Cells at most: the histogram beside the points and the bitmaps.
+__host__ __device__ inline int bq_cell_cap(int64_t N) { return N <= 6144 ? 4096 : 2048; }
+__host__ __device__ inline int bq_cell_lanes(int64_t N) { return N <= kBqCellSmallN ? 16 : 64; }
+static size_t bq_cell_lds(int64_t N) {
+    const int64_t gl = bq_cell_lanes(N);
+    return (size_t)(N * 16 + bq_cell_cap(N) * 4 + kBqCellWaves * 64 * 4 * ceil_div(ceil_div(N, 32), gl));
+}
+
+// Inclusive sums over rows of 16 lanes; over the wave.
+__device__ __forceinline__ int row_prefix_i32(int v) {
+    v += __builtin_amdgcn_mov_dpp(v, 0x111, 0xf, 0xf, true);                  // row_shr:1
+    v += __builtin_amdgcn_mov_dpp(v, 0x112, 0xf, 0xf, true);                  // row_shr:2
+    v += __builtin_amdgcn_mov_dpp(v, 0x114, 0xf, 0xf, true);                  // row_shr:4
+    v += __builtin_amdgcn_mov_dpp(v, 0x118, 0xf, 0xf, true);                  // row_shr:8
+    return v;
+}
+__device__ __forceinline__ int wave_prefix_i32(int v) {
+    v = row_prefix_i32(v);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);           // row_bcast:15 into rows 1, 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);           // row_bcast:31 into rows 2, 3
+    return v;
+}
+
+// Lane t's value of each group of GL lanes.
+template <int GL, int t>
+__device__ __forceinline__ int group_lane(int v) {
+    if constexpr (GL == 64) return __builtin_amdgcn_readlane(v, t);
+    else return __builtin_amdgcn_ds_swizzle(v, 0x10 | (t << 5));   // lane' = (lane & 16) | t
+}
+
+template <int GL, int PT>
+__global__ __launch_bounds__(64 * kBqCellWaves) void ball_query_cells_kernel(
+    const float* __restrict__ xyz, const float* __restrict__ qxyz, int N, int M, int wgs, int per, float radius,
+    float r2, int K, int walk_above, float dense, int32_t* __restrict__ nit, int32_t* __restrict__ cnt) {
+    constexpr int T = 64 * kBqCellWaves;
+    constexpr int QW = 64 / GL;                                    // queries per wave at a time
+    constexpr int WPL = (PT * T / 32 + GL - 1) / GL;               // bitmap words per lane at most
+    extern __shared__ float4 s_cells4[];
+    float4* s_pts = s_cells4;                                      // [N] x, y, z, index, grouped by cell
+    int* s_end = reinterpret_cast<int*>(s_pts + N);                // [cells] counts, starts, then ends
+    const int cap = bq_cell_cap(N);
+    const int words = (N + 31) >> 5, wpl = (words + GL - 1) / GL;  // bitmap words per lane
+    __shared__ float s_lo[kBqCellWaves][3], s_hi[kBqCellWaves][3];
+    __shared__ int s_wsum[kBqCellWaves];
+    __shared__ float s_sq[kBqCellWaves];
+    __shared__ int s_next;
+    __shared__ GridInfo s_gi;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int gl = lane & (GL - 1);                                // lane within its query's group
+    uint32_t* bits = reinterpret_cast<uint32_t*>(s_end + cap) + (wave * QW + lane / GL) * (wpl * GL);
+    const int64_t b = blockIdx.x / wgs;
+    const int q0 = (int)(blockIdx.x - b * wgs) * per, q1 = min(q0 + per, M);
+    const float* __restrict__ p = xyz + b * (int64_t)N * 3;
+
+    // 1. the cloud's box and the cells
+    float px[PT], py[PT], pz[PT];
+    int cell[PT];
+    float lo[3] = {__builtin_huge_valf(), __builtin_huge_valf(), __builtin_huge_valf()};
+    float hi[3] = {-__builtin_huge_valf(), -__builtin_huge_valf(), -__builtin_huge_valf()};
+#pragma unroll
+    for (int u = 0; u < PT; ++u) {
+        const int j = min(tid + u * T, N - 1);
+        px[u] = p[3 * j + 0];
+        py[u] = p[3 * j + 1];
+        pz[u] = p[3 * j + 2];
+        lo[0] = fminf(lo[0], px[u]); hi[0] = fmaxf(hi[0], px[u]);
+        lo[1] = fminf(lo[1], py[u]); hi[1] = fmaxf(hi[1], py[u]);
+        lo[2] = fminf(lo[2], pz[u]); hi[2] = fmaxf(hi[2], pz[u]);
+    }
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        lo[d] = wave_min_f32(lo[d]);
+        hi[d] = wave_max_f32(hi[d]);
+    }
+    if (lane == 0)
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            s_lo[wave][d] = lo[d];
+            s_hi[wave][d] = hi[d];
+        }
+    for (int c = tid; c < cap; c += T) s_end[c] = 0;
+    for (int i = gl; i < wpl * GL; i += GL) bits[i] = 0u;
+    if (tid == 0) s_next = q0;
+    // (the points in index order, in the space of the sorted ones, in case
+    // the queries walk)
+    float* sx = reinterpret_cast<float*>(s_pts);
+    float* sy = sx + N;
+    float* sz = sy + N;
+    auto keep_order = [&]() {
+#pragma unroll
+        for (int u = 0; u < PT; ++u) {
+            const int j = tid + u * T;
+            if (j < N) {
+                sx[j] = px[u];
+                sy[j] = py[u];
+                sz[j] = pz[u];
+            }
+        }
+    };
+    keep_order();
+    __syncthreads();
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        static_assert(kBqCellWaves == 16, "a row of lanes reduces the waves' boxes");
+        lo[d] = wave_min_f32(s_lo[lane & 15][d]);
+        hi[d] = wave_max_f32(s_hi[lane & 15][d]);
+    }
+    // Dense balls: where a query's 27 cells are expected to hold more than
+    // `dense` points (first: nine cells of a surface over the box's two
+    // longest axes; later: nine times the mean population of a point's own
+    // cell), the workgroup walks the cloud in index order for its queries.
+    bool walk_all;
+    GridInfo gi;
+    {
+        const float ir = 1.0f / radius;
+        const float ga = (hi[0] - lo[0]) * ir + 1.0f, gb = (hi[1] - lo[1]) * ir + 1.0f, gc = (hi[2] - lo[2]) * ir + 1.0f;
+        walk_all = 9.0f * (float)N > dense * (ga * gb * gc / fminf(ga, fminf(gb, gc)));
+    }
+    if (!walk_all) {
+        if (wave == 0) {
+            double mn[3], e[3];
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                mn[d] = lo[d];
+                e[d] = (double)hi[d] - (double)lo[d];
+            }
+            // the smallest cell edge from r (1 + 2^-12) up, in steps of 2^(1/4)
+            // (a lane each), whose cells fit; an eleventh of the widest extent
+            // always does (12^3 cells).  Non-finite coordinates put every point
+            // in one cell.
+            const double emax = fmax(e[0], fmax(e[1], e[2]));
+            if (!(emax < 1.0e300)) e[0] = e[1] = e[2] = 0.0;
+            const double hl = (double)radius * (1.0 + 1.0 / 4096.0) * (double)exp2f(0.25f * (float)lane);
+            const double il = 1.0 / hl;
+            // (reciprocals: a count may be one off where the quotient is whole,
+            // which only picks another edge; the cells are counted again below)
+            const double fit = (floor(e[0] * il) + 2.0) * (floor(e[1] * il) + 2.0) * (floor(e[2] * il) + 2.0);
+            const uint64_t ok = ballot(fit <= (double)cap);
+            const double last = __shfl(hl, 63);
+            const double h = ok ? __shfl(hl, __builtin_ctzll(ok)) : fmax(last, emax / 11.0);
+            if (lane == 0) {
+                GridInfo gi;
+#pragma unroll
+                for (int d = 0; d < 3; ++d) {
+                    gi.mn[d] = mn[d];
+                    gi.g[d] = (int)(floor(e[d] / h) + 1.0);
+                }
+                gi.inv_h = 1.0 / h;
+                gi.radius = radius;
+                s_gi = gi;
+            }
+        }
+        __syncthreads();
+        gi = s_gi;
+        // 2. counts, starts, and the points into their cells (any order inside)
+#pragma unroll
+        for (int u = 0; u < PT; ++u) {
+            cell[u] = grid_cell(gi, px[u], py[u], pz[u]);
+            if (tid + u * T < N) atomicAdd(&s_end[cell[u]], 1);
+        }
+        __syncthreads();
+        const int cpt = cap / T;   // 4 or 2
+        int sum = 0;
+        float squares = 0.0f;
+        for (int c = 0; c < cpt; ++c) {
+            const int k = s_end[tid * cpt + c];
+            sum += k;
+            squares += (float)k * (float)k;
+        }
+        const int incl = wave_prefix_i32(sum);
+        for (int o = 32; o > 0; o >>= 1) squares += __shfl_xor(squares, o);
+        if (lane == 63) {
+            s_wsum[wave] = incl;
+            s_sq[wave] = squares;
+        }
+        __syncthreads();
+        squares = 0.0f;
+#pragma unroll
+        for (int v = 0; v < kBqCellWaves; ++v) squares += s_sq[v];
+        walk_all = 9.0f * squares > dense * (float)N;
+        int off = incl - sum;
+        for (int v = 0; v < wave; ++v) off += s_wsum[v];
+        for (int c = 0; c < cpt; ++c) {
+            const int k = s_end[tid * cpt + c];
+            s_end[tid * cpt + c] = off;
+            off += k;
+        }
+        __syncthreads();
+    }
+    if (walk_all) {
+        for (;;) {   // waves take the queries as they come free
+            int qi = 0;
+            if (lane == 0) qi = atomicAdd(&s_next, 1);
+            qi = __builtin_amdgcn_readfirstlane(qi);
+            if (qi >= q1) break;
+            const int64_t gq = b * M + qi;
+            auto pt = [&](int j, float& x, float& y, float& z) {
+                x = sx[j];
+                y = sy[j];
+                z = sz[j];
+            };
+            const int n =
+                bq_walk(pt, N, qxyz[gq * 3 + 0], qxyz[gq * 3 + 1], qxyz[gq * 3 + 2], r2, K, nit + gq * K, lane);
+            if (cnt && lane == 0) cnt[gq] = n;
+        }
+        return;
+    }
+#pragma unroll
+    for (int u = 0; u < PT; ++u) {
+        const int j = tid + u * T;
+        if (j < N) s_pts[atomicAdd(&s_end[cell[u]], 1)] = make_float4(px[u], py[u], pz[u], __int_as_float(j));
+    }
+    __syncthreads();
+
+    // 3. QW queries per wave at a time
+    for (int qw = q0 + wave * QW; qw < q1; qw += kBqCellWaves * QW) {
+        const int qi = qw + lane / GL;
+        const bool real = qi < q1;
+        const int64_t gq = b * M + min(qi, q1 - 1);
+        const float qx = qxyz[gq * 3 + 0], qy = qxyz[gq * 3 + 1], qz = qxyz[gq * 3 + 2];
+        const int cx = grid_coord(qx, gi.mn[0], gi.inv_h);
+        const int cy = grid_coord(qy, gi.mn[1], gi.inv_h);
+        const int cz = grid_coord(qz, gi.mn[2], gi.inv_h);
+        const int x0 = max(cx - 1, 0), x1 = min(cx + 1, gi.g[0] - 1);
+        const int y0 = max(cy - 1, 0), y1 = min(cy + 1, gi.g[1] - 1);
+        const int z0 = max(cz - 1, 0), z1 = min(cz + 1, gi.g[2] - 1);
+        // lane t < 9 of the group one row of cells: the points [rs, rs + rn)
+        int rs = 0, rn = 0;
+        if (real && x0 <= x1 && gl < 9) {
+            const int y = y0 + gl % 3, z = z0 + gl / 3;
+            if (y <= y1 && z <= z1) {
+                const int row = (z * gi.g[1] + y) * gi.g[0];
+                rs = row + x0 > 0 ? s_end[row + x0 - 1] : 0;
+                rn = s_end[row + x1] - rs;
+            }
+        }
+        const int rp = row_prefix_i32(rn);
+        const int cand = group_lane<GL, 8>(rp);
+        int32_t* __restrict__ out = nit + gq * K;
+        const bool dense = cand > walk_above;   // the index-order walk ends early
+        if (const uint64_t walks = ballot(dense)) {
+            for (int q = 0; q < QW; ++q) {
+                const int l = q * GL;
+                if (!((walks >> l) & 1)) continue;
+                auto pt = [&](int j, float& x, float& y, float& z) {
+                    x = p[3 * j + 0];
+                    y = p[3 * j + 1];
+                    z = p[3 * j + 2];
+                };
+                const int64_t g = b * M + qw + q;
+                const int n = bq_walk(pt, N, __int_as_float(__builtin_amdgcn_readlane(__float_as_int(qx), l)),
+                                      __int_as_float(__builtin_amdgcn_readlane(__float_as_int(qy), l)),
+                                      __int_as_float(__builtin_amdgcn_readlane(__float_as_int(qz), l)), r2, K,
+                                      nit + g * K, lane);
+                if (cnt && lane == 0) cnt[g] = n;
+            }
+            if (walks == ~0ull) continue;
+            rn = dense ? 0 : rn;
+        }
+        auto test = [&](int i) {
+            const float4 pt = s_pts[i];
+            const int j = __float_as_int(pt.w);
+            if (dist3(pt.x, pt.y, pt.z, qx, qy, qz) < r2) atomicOr(bits + (j >> 5), 1u << (j & 31));
+        };
+        if constexpr (GL == 64) {
+            // all nine rows at once, 64 candidates per pass
+            int rend[9], rdelta[9];
+#pragma unroll
+            for (int t = 0; t < 9; ++t) {
+                rend[t] = __builtin_amdgcn_readlane(rp, t);
+                rdelta[t] = __builtin_amdgcn_readlane(rs, t) - (rend[t] - __builtin_amdgcn_readlane(rn, t));
+            }
+            for (int c = lane; c < cand; c += 64) {
+                int i = c + rdelta[8];
+#pragma unroll
+                for (int t = 7; t >= 0; --t) i = c < rend[t] ? c + rdelta[t] : i;
+                test(i);
+            }
+        } else {
+            // row by row: a row holds about as many points as there are lanes
+            int start[9], end[9];
+            const int re = rs + rn;
+            start[0] = group_lane<GL, 0>(rs); end[0] = group_lane<GL, 0>(re);
+            start[1] = group_lane<GL, 1>(rs); end[1] = group_lane<GL, 1>(re);
+            start[2] = group_lane<GL, 2>(rs); end[2] = group_lane<GL, 2>(re);
+            start[3] = group_lane<GL, 3>(rs); end[3] = group_lane<GL, 3>(re);
+            start[4] = group_lane<GL, 4>(rs); end[4] = group_lane<GL, 4>(re);
+            start[5] = group_lane<GL, 5>(rs); end[5] = group_lane<GL, 5>(re);
+            start[6] = group_lane<GL, 6>(rs); end[6] = group_lane<GL, 6>(re);
+            start[7] = group_lane<GL, 7>(rs); end[7] = group_lane<GL, 7>(re);
+            start[8] = group_lane<GL, 8>(rs); end[8] = group_lane<GL, 8>(re);
+#pragma unroll
+            for (int t = 0; t < 9; ++t)
+                for (int i = start[t] + gl; i < end[t]; i += GL) test(i);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        // the first K set bits in index order, each lane its words, which are
+        // cleared for the next query
+        uint32_t m[WPL];
+        int pc = 0;
+#pragma unroll
+        for (int i = 0; i < WPL; ++i) {
+            m[i] = 0u;
+            if (i < wpl) {
+                m[i] = bits[gl * wpl + i];
+                bits[gl * wpl + i] = 0u;
+                pc += __builtin_popcount(m[i]);
+            }
+        }
+        const int incl = GL == 64 ? wave_prefix_i32(pc) : row_prefix_i32(pc);
+        const int total = group_lane<GL, GL - 1>(incl);
+        int rank = incl - pc, lowest = 0;
+#pragma unroll
+        for (int i = WPL - 1; i >= 0; --i)
+            if (m[i]) lowest = ((gl * wpl + i) << 5) + __builtin_ctz(m[i]);
+        const uint64_t has = ballot(pc > 0);
+        const uint64_t mine = GL == 64 ? has : (has >> (lane & ~(GL - 1))) & ((1ull << (GL & 63)) - 1);
+        const int first = __shfl(lowest, (lane & ~(GL - 1)) + (mine ? __builtin_ctzll(mine) : 0));
+        if (real && !dense) {
+#pragma unroll
+            for (int i = 0; i < WPL; ++i) {
+                while (m[i] && rank < K) {
+                    out[rank++] = ((gl * wpl + i) << 5) + __builtin_ctz(m[i]);
+                    m[i] &= m[i] - 1u;
+                }
+            }
+            const int n = min(total, K);
+            const int pad = total > 0 ? first : 0;
+            for (int k = n + gl; k < K; k += GL) out[k] = pad;
+            if (cnt && gl == 0) cnt[gq] = n;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    }
+}
+
+static int bq_cus() {
+    int dev = 0, cus = 256;
+    if (hipGetDevice(&dev) == hipSuccess) {
+        int v = 0;
+        if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0) cus = v;
+    }
+    return cus;
+}
+
+// walk or grid: a ball of c candidates holds about 0.155 c points (sphere over
+// 27 cubes), so a walk scans about K N / (0.155 c); the two cost the same near
+// c = sqrt(6.45 K N).  With 16 lanes per query the walks of a wave's four
+// queries run one after another, and pay from twice that.
+static int bq_walk_above(int64_t N, int32_t K, int lanes = 64) {
+    const double c = std::sqrt(6.45 * (double)K * (double)N);
+    return (int)std::min(lanes == 64 ? c : 2.0 * c, 2.0e9);
+}
+
+static int launch_bq_cells(const float* xyz, const float* qxyz, int64_t B, int64_t N, int64_t M, float radius,
+                           int32_t K, int32_t* nit, int32_t* cnt, hipStream_t s, const char* who) {
+    // one workgroup per CU, a multiple of 16 waves' queries each
+    const int lanes = bq_cell_lanes(N), at_once = kBqCellWaves * 64 / lanes;
+    const int64_t share = std::max<int64_t>(1, bq_cus() / B);
+    const int64_t per = ceil_div(ceil_div(M, share), at_once) * at_once;
+    const int64_t wgs = ceil_div(M, per);
+    MESO_REQUIRE(B * wgs <= 0x7fffffff, MESORASI_EUNSUPPORTED, "%s: too many queries", who);
+    auto launch = [&](auto lanes_c, auto points_c) {
+        constexpr int GL = decltype(lanes_c)::value, PT = decltype(points_c)::value;
+        static const hipError_t attr =
+            hipFuncSetAttribute(reinterpret_cast<const void*>(&ball_query_cells_kernel<GL, PT>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, 159 * 1024);
+        MESO_REQUIRE(attr == hipSuccess, MESORASI_EHIP, "%s: LDS size attribute: %s", who, hipGetErrorString(attr));
+        ball_query_cells_kernel<GL, PT><<<dim3((unsigned)(B * wgs)), dim3(64 * kBqCellWaves), bq_cell_lds(N), s>>>(
+            xyz, qxyz, (int)N, (int)M, (int)wgs, (int)per, radius, radius * radius, K, bq_walk_above(N, K, GL),
+            kBqDense * (float)bq_walk_above(N, K), nit, cnt);
+        return after_launch(who);
+    };
+    using std::integral_constant;
+    if (N <= 2048) return launch(integral_constant<int, 16>(), integral_constant<int, 2>());
+    if (N <= 4096) return launch(integral_constant<int, 16>(), integral_constant<int, 4>());
+    if (N <= kBqCellSmallN) return launch(integral_constant<int, 16>(), integral_constant<int, 5>());
+    return launch(integral_constant<int, 64>(), integral_constant<int, 8>());
+}
+
 static size_t grid_ws_bytes(int64_t B, int64_t N) {
     if (B <= 0 || N <= 0) return 0;
     auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
@@ -430,10 +839,7 @@ static int launch_grid_query(const float* xyz, const float* qxyz, int64_t B, int
     const int64_t qblocks = ceil_div(BM, kGridQWaves);
     MESO_REQUIRE(qblocks <= 0x7fffffff, MESORASI_EUNSUPPORTED, "%s: too many queries", who);
     const size_t lds = (size_t)kGridQWaves * 64 * ceil_div(ceil_div(N, 32), 64) * 4;
-    // walk or grid: a ball of c candidates holds about 0.155 c points
-    // (sphere over 27 cubes), so a walk scans about K N / (0.155 c);
-    // the two cost the same near c = sqrt(6.45 K N)
-    const int walk_above = (int)std::min(std::sqrt(6.45 * (double)K * (double)N), 2.0e9);
+    const int walk_above = bq_walk_above(N, K);
     grid_query_kernel<<<dim3((unsigned)qblocks), dim3(64 * kGridQWaves), lds, s>>>(
         xyz, qxyz, BM, (int)N, (int)M, radius, radius * radius, K, walk_above, w, nit, cnt);
     return after_launch(who);
@@ -484,6 +890,8 @@ extern "C" int mesorasi_ball_query(const float* xyz, const float* qxyz, int64_t 
         if (rc != MESORASI_OK) return rc;
         return launch_grid_query(xyz, qxyz, B, N, M, radius, K, nit, cnt, w, s, who);
     }
+    if (N >= kBqCellMinN && N <= kBqCellMaxN && BM * ceil_div(N, 64 * kBqChunks) >= kBqCellMinSteps)
+        return launch_bq_cells(xyz, qxyz, B, N, M, radius, K, nit, cnt, s, who);
     if (N >= kBqLdsMinN) {
         // below kBqGridMinN points: 3 N floats of LDS, at most 96 KB
         const int64_t qb = ceil_div(M, kBqLdsWaves);

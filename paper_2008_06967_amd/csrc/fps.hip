@@ -376,32 +376,6 @@ static void launch_fps_lds(const float* xyz, int64_t B, int N, int M, int32_t* i
 // would not fit beside the ring).
 // ---------------------------------------------------------------------------
 
-// Float min / max over the wave (all lanes active), uniform result.
-template <int CTRL>
-__device__ __forceinline__ float dpp_f32(float v) {
-    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, false));
-}
-
-__device__ __forceinline__ float wave_min_f32(float v) {
-    v = fminf(v, dpp_f32<0x121>(v));
-    v = fminf(v, dpp_f32<0x122>(v));
-    v = fminf(v, dpp_f32<0x124>(v));
-    v = fminf(v, dpp_f32<0x128>(v));
-    v = fminf(v, __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), 0x142, 0xa, 0xf, false)));
-    v = fminf(v, __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), 0x143, 0xc, 0xf, false)));
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
-}
-
-__device__ __forceinline__ float wave_max_f32(float v) {
-    v = fmaxf(v, dpp_f32<0x121>(v));
-    v = fmaxf(v, dpp_f32<0x122>(v));
-    v = fmaxf(v, dpp_f32<0x124>(v));
-    v = fmaxf(v, dpp_f32<0x128>(v));
-    v = fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), 0x142, 0xa, 0xf, false)));
-    v = fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), 0x143, 0xc, 0xf, false)));
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
-}
-
 // Int min over the wave (rare tie paths only).
 __device__ __forceinline__ int wave_min_i32_shfl(int v) {
 #pragma unroll

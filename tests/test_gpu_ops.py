@@ -222,6 +222,17 @@ BQ_CASES = [
     ("grid_two_far_clusters", 1, 12000, 400, 0.05, 16, "clusters"),   # 32 cells per axis cap: cells wider than r
     ("grid_queries_outside", 2, 8192, 300, 0.5, 32, "outside"),
     ("grid_n_max", 1, 65536, 256, 0.1, 64, "normal"),
+    # many queries of 1025 .. 8191 points: cells in LDS, 16 lanes or a wave per query
+    ("cells_1025", 20, 1025, 1025, 0.3, 16, "normal"),
+    ("cells_2048_grid", 16, 2048, 1000, 1.0, 32, "grid"),      # points at exactly distance r
+    ("cells_4096_mesh", 8, 4096, 1024, 0.1, 32, "mesh"),
+    ("cells_4096_k1", 8, 4096, 1030, 0.1, 1, "cube"),
+    ("cells_4097_k1024", 8, 4097, 1000, 0.9, 1024, "normal"),
+    ("cells_4500_dense", 7, 4500, 1000, 3.0, 64, "mesh"),      # every ball dense: the index-order walk
+    ("cells_5120_outside", 6, 5120, 1100, 0.7, 32, "outside"),
+    ("cells_5121_clusters", 6, 5121, 1000, 0.05, 32, "clusters"),
+    ("cells_6145_outlier", 6, 6145, 1000, 0.3, 32, "outlier"),  # all but one point in one cell
+    ("cells_8191_dups", 4, 8191, 1000, 0.2, 64, "dups"),
 ]
 
 

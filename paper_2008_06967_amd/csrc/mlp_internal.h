@@ -49,11 +49,10 @@ int run_fused_mlp(const float* x0, int c0, int64_t ld0, const float* x1, int c1,
                   const MlpGather* g = nullptr);
 
 // True when every layer is at most 128 wide (the register-resident MLP,
-// mlp_rr.hip) and either the permuted weights of all layers fit the LDS of
-// one workgroup, or each fits and the rows make at most one 32-row tile
-// per wave (the weights are then staged in phases).  The second form knows
-// the first layer's sources: one of at most 8 channels beside an aligned
-// one of whole 4-channel chunks adds to the 128.
+// mlp_rr.hip) and either the layers' fp32 weights make at most 160 KB, or
+// the rows make at most one 32-row tile per wave.  The second form knows the
+// first layer's sources: one of at most 8 channels beside an aligned one of
+// whole 4-channel chunks adds to the 128.
 bool rr_mlp_supported(int n_layers, const int32_t* dims, int64_t rows);
 bool rr_mlp_supported(const float* x0, int c0, int64_t ld0, const float* x1, int c1, int64_t ld1, int n_layers,
                       const int32_t* dims, int64_t rows);

@@ -7,18 +7,36 @@
 // intermediate activation and stages it through LDS.
 //
 // Each wave pushes 32-row tiles through every layer on its own.  The
-// product is taken transposed, Y^T = W X^T, on v_mfma_f32_32x32x2_f32: the
-// weights are the A operand (32 output channels x 2 k) and the activations
-// the B operand (2 k x 32 rows), so a lane's 16 accumulators of a 32-channel
-// block hold 16 output channels of ONE row, its lane % 32 (channel 8(r/4) +
-// 4(lane/32) + r%4 of register r).  An MFMA sums over whatever k order its
-// two operands share, so the next layer takes its k steps in exactly that
-// register order: step (j, r) is the k pair {32j + 8(r/4) + r%4, +4}, lane
-// half h supplying its own accumulator r of block j.  The activations never
-// leave registers between layers: no LDS round trip, no barrier, no
-// transpose.  The weights, permuted once per workgroup into each layer's k
-// order, are the only LDS data: a workgroup is persistent, loads every
-// layer's weights and biases once, and its eight waves then stream tiles.
+// product is taken transposed, Y^T = W X^T, on MFMAs of 32 x 32 outputs: the
+// weights are the A operand (32 output channels) and the activations the B
+// operand (32 rows), so a lane's 16 accumulators of a 32-channel block hold
+// 16 output channels of ONE row, its lane % 32 (channel 8(r/4) + 4(lane/32)
+// + r%4 of register r).  An MFMA sums over whatever k order its two operands
+// share, so the next layer takes its k steps in exactly that register order:
+// step (j, r) is the k pair {32j + 8(r/4) + r%4, +4}, lane half h supplying
+// its own accumulator r of block j.  The activations never leave registers
+// between layers: no LDS round trip, no barrier, no transpose.  The weights,
+// permuted once per workgroup into each layer's k order, are the only LDS
+// data: a workgroup is persistent, its eight waves stream tiles.
+//
+// The fp32 matrix instruction bounded this kernel (65536 x 131 -> 128 -> 128
+// -> 128: 41 of 77 us; it runs at a sixteenth of the bf16 rate).  So every
+// fp32 value is taken as the exact sum of three bf16 values (24 = 3 x 8 bits
+// of mantissa, each part rounded to nearest) and a product as the six
+// partial products of at least 2^-18 of it, on v_mfma_f32_32x32x16_bf16 with
+// fp32 sums: eight k steps of a lane half make one of these instructions.
+// The three products left out are below 2^-25 of the product together, less
+// than the rounding of one fp32 sum, and there are fewer of those (six per
+// 16 k instead of sixteen).  The parts of huge values would overflow, those of
+// infinities would be NaN and those of very small ones denormal, so a tile
+// whose weights or activations hold such values is multiplied by
+// v_mfma_f32_32x32x2_f32 on the same operands, the weights put together
+// again (rr_products_plain).
+// Measured: 524288 gathered rows 3 -> 64 -> 64 -> 128, pooled: 128 -> 103 us;
+// 65536 x 131 -> 128 -> 128 -> 128: 77 -> 57 us with its launch; error against
+// 64 bits 1.3e-7 -> 7e-8 and 2.8e-7 -> 1.2e-7 (2-norm).  What bounds it now is
+// the split (44 vector instructions per 16 k of a row) and the LDS reads of the
+// weights, not yet the matrix cores (33 and 16 us).
 // The first layer reads its rows straight from memory, the two lanes of a
 // row taking alternate 4-channel chunks.  Its input may have two parts: a
 // wide source of whole aligned 4-channel chunks, and a narrow one of at most
@@ -31,6 +49,7 @@
 // lane's accumulators are reduced over the lanes of its half wave (16), so
 // the rows' outputs are neither stored nor cleared beforehand.
 #include <algorithm>
+#include <array>
 
 #include "common.h"
 #include "mlp_internal.h"
@@ -40,11 +59,14 @@ namespace meso {
 namespace {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 constexpr int kRrWaves = 8;          // waves per workgroup (two per SIMD)
 constexpr int kRrMaxWidth = 128;     // widest layer input or output
 constexpr int kRrMaxSteps = 64;      // k steps of a layer (128 inputs / 2)
 constexpr int kRrMaxLds = 160 * 1024;
+constexpr float kRrHuge = 0x1p120f, kRrSmall = 0x1p-80f;   // the range in which the bf16 parts are exact
 
 struct RrArgs {
     const float* x0;
@@ -60,10 +82,10 @@ struct RrArgs {
     const float* bias[MESORASI_MAX_LAYERS];
     int woff[MESORASI_MAX_LAYERS];   // float offset of layer l's permuted weights in LDS
     int boff[MESORASI_MAX_LAYERS];   // float offset of its padded bias
-    int lds_floats;
+    int foff;                        // int offset of the waves' flags (a weight out of the split's range)
     // weights staged in phases when all layers do not fit at once: phase p
     // holds layers phase_first[p] .. phase_first[p + 1] - 1 (offsets above
-    // relative to the phase); then every wave holds at most one tile
+    // relative to the phase)
     int nphase;
     int phase_first[MESORASI_MAX_LAYERS + 1];
     uint32_t relu_mask;
@@ -88,11 +110,18 @@ struct RrArgs {
 };
 
 __host__ __device__ inline int rr_blocks(int n) { return (n + 31) / 32; }
-// k steps of layer l: 16 per 32-channel input block; the first layer's
-// half-rows are padded to whole blocks of 16 steps too (k0h = 16 nj), and its
-// narrow source takes 4 ahead of them
-__host__ __device__ inline int rr_steps(const int* dims, int l, int k0h, int cs) {
-    return l == 0 ? k0h + (cs > 0 ? 4 : 0) : 16 * rr_blocks(dims[l]);
+// bf16 steps (of 16 k) of layer l: 2 per 32-channel input block; the first
+// layer's wide source is padded to whole blocks too (k0h = 16 nj k per lane
+// half).
+__host__ __device__ inline int rr_steps(const int* dims, int l, int k0h) {
+    return l == 0 ? k0h / 8 : 2 * rr_blocks(dims[l]);
+}
+// LDS floats of layer l: the narrow source's weights as fp32 (64 lanes x 4
+// per output block), the others as three bf16 parts, the bias.
+__host__ __device__ inline int rr_narrow_floats(int nob, int l, int cs) { return l == 0 && cs > 0 ? nob * 256 : 0; }
+inline int rr_floats(const int* dims, int l, int k0h, int cs) {
+    const int nob = rr_blocks(dims[l + 1]);
+    return rr_narrow_floats(nob, l, cs) + nob * rr_steps(dims, l, k0h) * 3 * 256 + nob * 32;
 }
 
 // The input channel that lane half h supplies at k step s of layer l.
@@ -104,63 +133,173 @@ __device__ __forceinline__ int rr_k(int l, int s, int h) {
     return 32 * j + 8 * (r >> 2) + (r & 3) + 4 * h;
 }
 
-// One layer's products: NJ input blocks of 16 k steps, NOB output blocks
-// whose weights lie `ng` groups of four steps apart, the output blocks'
-// accumulation chains interleaved step by step.
-template <int NJ, int NOB>
-__device__ __forceinline__ void rr_products(const float4* __restrict__ wl, int ng, const float (&act)[kRrMaxSteps],
+// Two floats to bf16, round to nearest even, the first in the low half.
+__device__ __forceinline__ uint32_t rr_pack(float lo, float hi) {
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    const f32x2 v = {lo, hi};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+}
+__device__ __forceinline__ float rr_low(uint32_t w) { return __uint_as_float(w << 16); }
+__device__ __forceinline__ float rr_high(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
+
+// Pins eight values to this point of the program: what is computed from them
+// is computed here, not for all steps at once ahead of the products (which
+// spilled more registers than the products use).
+__device__ __forceinline__ void rr_here(float* v) {
+    asm volatile("" : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]), "+v"(v[7]));
+}
+
+// Eight floats as three vectors of bf16 parts, p[0] + p[1] + p[2] = v.
+__device__ __forceinline__ void rr_split(const float* v, uint4 (&p)[3]) {
+    uint32_t w[3][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        float x = v[2 * i], y = v[2 * i + 1];
+        w[0][i] = rr_pack(x, y);
+        x -= rr_low(w[0][i]);
+        y -= rr_high(w[0][i]);
+        w[1][i] = rr_pack(x, y);
+        x -= rr_low(w[1][i]);
+        y -= rr_high(w[1][i]);
+        w[2][i] = rr_pack(x, y);
+    }
+#pragma unroll
+    for (int q = 0; q < 3; ++q) p[q] = make_uint4(w[q][0], w[q][1], w[q][2], w[q][3]);
+}
+
+// One weight outside the range of rr_split: parts that sum to it exactly,
+// none of them rounded up to infinity.
+__device__ __forceinline__ void rr_split_huge(float v, uint32_t (&p)[3]) {
+    p[1] = p[2] = 0;
+    if (v != v) p[0] = 0x7fc0u;
+    else {
+        const uint32_t u = __float_as_uint(v);
+        p[0] = u >> 16;
+        if ((u & 0x7f800000u) == 0x7f800000u) return;
+        const float r = v - __uint_as_float(u & 0xffff0000u);
+        const uint32_t ur = __float_as_uint(r);
+        p[1] = ur >> 16;
+        p[2] = __float_as_uint(r - __uint_as_float(ur & 0xffff0000u)) >> 16;
+    }
+}
+
+__device__ __forceinline__ bf16x8 rr_bf16x8(uint4 v) { return __builtin_bit_cast(bf16x8, v); }
+
+// A step's weights of two output blocks (the second clamped to the first where
+// there is none).
+__device__ __forceinline__ void rr_weights(const uint4* __restrict__ wl, int stride, uint4 (&w)[2][3]) {
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int q = 0; q < 3; ++q) w[b][q] = wl[b * stride + q * 64];
+}
+
+// A step's five small partial products on NB output blocks, whose
+// accumulation chains interleave.
+template <int NB>
+__device__ __forceinline__ void rr_small(const uint4 (&w)[2][3], const uint4 (&x)[3], f32x16* __restrict__ acc) {
+    constexpr int pw[5] = {2, 0, 1, 1, 0}, px[5] = {0, 2, 1, 0, 1};
+#pragma unroll
+    for (int m = 0; m < 5; ++m)
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+            acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rr_bf16x8(w[b][pw[m]]), rr_bf16x8(x[px[m]]), acc[b], 0, 0,
+                                                             0);
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// One layer's products: nt steps, nob output blocks, taken in pairs.  All the
+// small partial products are summed first and the large ones after them, so
+// that only one rounding per 16 k is a rounding of a large sum.  A pair's
+// weights are requested ahead of the split of its activations or of the other
+// pair's products.  (The steps and blocks are guarded, not switched over: one
+// instance is in the kernel, and the activations keep their registers around
+// it; sixteen instances spilled them.)
+__device__ __forceinline__ void rr_products(int nt, int nob, const uint4* __restrict__ wl, float (&act)[kRrMaxSteps],
                                             f32x16 (&acc)[kRrMaxWidth / 32]) {
-    float4 w[NOB];
+    static_assert(kRrMaxWidth == 128, "two pairs of output blocks");
+    const int stride = nt * 3 * 64;
 #pragma unroll
-    for (int ob = 0; ob < NOB; ++ob) w[ob] = wl[ob * ng * 64];
-#pragma unroll
-    for (int g = 0; g < 4 * NJ; ++g) {
-        // the next group's weights are requested before this group's MFMAs
-        float4 wn[NOB];
-        if (g + 1 < 4 * NJ) {
-#pragma unroll
-            for (int ob = 0; ob < NOB; ++ob) wn[ob] = wl[(ob * ng + g + 1) * 64];
+    for (int t = 0; t < kRrMaxSteps / 8; ++t) {
+        if (t < nt) {
+            const uint4* wt = wl + t * 3 * 64;
+            uint4 w0[2][3], x[3];
+            rr_weights(wt, nob > 1 ? stride : 0, w0);
+            __builtin_amdgcn_sched_barrier(0);
+            rr_here(&act[8 * t]);
+            rr_split(&act[8 * t], x);
+            if (nob > 2) {
+                uint4 w1[2][3];
+                rr_weights(wt + 2 * stride, nob > 3 ? stride : 0, w1);
+                __builtin_amdgcn_sched_barrier(0);
+                rr_small<2>(w0, x, &acc[0]);
+                if (nob > 3) rr_small<2>(w1, x, &acc[2]);
+                else rr_small<1>(w1, x, &acc[2]);
+            } else {
+                __builtin_amdgcn_sched_barrier(0);
+                if (nob > 1) rr_small<2>(w0, x, &acc[0]);
+                else rr_small<1>(w0, x, &acc[0]);
+            }
         }
-        __builtin_amdgcn_sched_barrier(0);
+    }
+    uint4 v[kRrMaxWidth / 32];
 #pragma unroll
-        for (int ob = 0; ob < NOB; ++ob)
-            acc[ob] = __builtin_amdgcn_mfma_f32_32x32x2f32(w[ob].x, act[4 * g + 0], acc[ob], 0, 0, 0);
+    for (int ob = 0; ob < kRrMaxWidth / 32; ++ob) v[ob] = wl[(ob < nob ? ob : 0) * stride];
 #pragma unroll
-        for (int ob = 0; ob < NOB; ++ob)
-            acc[ob] = __builtin_amdgcn_mfma_f32_32x32x2f32(w[ob].y, act[4 * g + 1], acc[ob], 0, 0, 0);
+    for (int t = 0; t < kRrMaxSteps / 8; ++t) {
+        if (t < nt) {
+            uint4 vn[kRrMaxWidth / 32];
+            const uint4* wt = wl + (t + 1 < nt ? t + 1 : t) * 3 * 64;
 #pragma unroll
-        for (int ob = 0; ob < NOB; ++ob)
-            acc[ob] = __builtin_amdgcn_mfma_f32_32x32x2f32(w[ob].z, act[4 * g + 2], acc[ob], 0, 0, 0);
+            for (int ob = 0; ob < kRrMaxWidth / 32; ++ob) vn[ob] = wt[(ob < nob ? ob : 0) * stride];
+            rr_here(&act[8 * t]);   // (rounded again, not held in registers since the first loop)
+            const float* z = &act[8 * t];
+            const uint4 x0 = make_uint4(rr_pack(z[0], z[1]), rr_pack(z[2], z[3]), rr_pack(z[4], z[5]),
+                                        rr_pack(z[6], z[7]));
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int ob = 0; ob < NOB; ++ob)
-            acc[ob] = __builtin_amdgcn_mfma_f32_32x32x2f32(w[ob].w, act[4 * g + 3], acc[ob], 0, 0, 0);
-        // keeps the compiler from hoisting every group's weights at once
-        __builtin_amdgcn_sched_barrier(0);
-        if (g + 1 < 4 * NJ) {
+            for (int ob = 0; ob < kRrMaxWidth / 32; ++ob)
+                if (ob < nob)
+                    acc[ob] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rr_bf16x8(v[ob]), rr_bf16x8(x0), acc[ob], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int ob = 0; ob < NOB; ++ob) w[ob] = wn[ob];
+            for (int ob = 0; ob < kRrMaxWidth / 32; ++ob) v[ob] = vn[ob];
         }
     }
 }
 
-template <int NJ>
-__device__ __forceinline__ void rr_products_nob(int nob, const float4* __restrict__ wl, int ng,
-                                                const float (&act)[kRrMaxSteps], f32x16 (&acc)[kRrMaxWidth / 32]) {
-    switch (nob) {
-        case 1: rr_products<NJ, 1>(wl, ng, act, acc); break;
-        case 2: rr_products<NJ, 2>(wl, ng, act, acc); break;
-        case 3: rr_products<NJ, 3>(wl, ng, act, acc); break;
-        default: rr_products<NJ, 4>(wl, ng, act, acc); break;
+// The same products on the fp32 instruction, for values outside the range of
+// rr_split (not a path that sizes or ordinary values reach).
+__device__ __forceinline__ void rr_products_plain(int nt, int nob, const uint4* __restrict__ wl,
+                                                  const float (&act)[kRrMaxSteps], f32x16 (&acc)[kRrMaxWidth / 32]) {
+#pragma unroll
+    for (int t = 0; t < kRrMaxSteps / 8; ++t) {
+        if (t < nt) {
+#pragma unroll
+            for (int ob = 0; ob < kRrMaxWidth / 32; ++ob) {
+                if (ob < nob) {
+                    const uint32_t* p = reinterpret_cast<const uint32_t*>(wl + (ob * nt + t) * 3 * 64);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        const uint32_t a0 = p[e >> 1], a1 = p[256 + (e >> 1)], a2 = p[512 + (e >> 1)];
+                        const float w = e & 1 ? rr_high(a0) + (rr_high(a1) + rr_high(a2))
+                                              : rr_low(a0) + (rr_low(a1) + rr_low(a2));
+                        acc[ob] = __builtin_amdgcn_mfma_f32_32x32x2f32(w, act[8 * t + e], acc[ob], 0, 0, 0);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+        }
     }
 }
 
 // The narrow source's four steps.
-__device__ __forceinline__ void rr_narrow(int nob, const float4* __restrict__ wl, int ng, const float (&sm)[4],
+__device__ __forceinline__ void rr_narrow(int nob, const float4* __restrict__ wl, const float (&sm)[4],
                                           f32x16 (&acc)[kRrMaxWidth / 32]) {
 #pragma unroll
     for (int ob = 0; ob < kRrMaxWidth / 32; ++ob) {
         if (ob < nob) {
-            const float4 w = wl[ob * ng * 64];
+            const float4 w = wl[ob * 64];
             acc[ob] = __builtin_amdgcn_mfma_f32_32x32x2f32(w.x, sm[0], acc[ob], 0, 0, 0);
             acc[ob] = __builtin_amdgcn_mfma_f32_32x32x2f32(w.y, sm[1], acc[ob], 0, 0, 0);
             acc[ob] = __builtin_amdgcn_mfma_f32_32x32x2f32(w.z, sm[2], acc[ob], 0, 0, 0);
@@ -180,8 +319,8 @@ __device__ __forceinline__ float rr_relu(float v) {
 // epilogue, the other keeps the SIMD's MFMA pipe busy.  (A four-wave form
 // with 512 registers per wave that requested its next tile's rows before
 // computing the current one measured 9-18 % slower.)
-// PHASED: the weights staged in phases, at most one tile per wave.  POOLED:
-// gathered neighbor rows, the output their max per centroid.
+// PHASED: the weights staged in phases.  POOLED: gathered neighbor rows, the
+// output their max per centroid.
 template <bool PHASED, bool POOLED>
 __global__ __launch_bounds__(64 * kRrWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void mlp_rr_kernel(RrArgs a) {
@@ -321,55 +460,107 @@ void mlp_rr_kernel(RrArgs a) {
     const int64_t t0 = wg * kRrWaves + wave;
     if (t0 < a.tiles) load_tile(t0, act);
 
-    // weights: layer l, output block ob, step group g = s / 4, lane, s % 4;
-    // thread tid fills float4s tid + 512 u (at most 4 blocks x 17
-    // groups x 64 lanes), each 4 consecutive k of one weight row; all of a
-    // layer's loads are in flight before the first LDS store
-    constexpr int kPer = (4 * 17 * 64 + 64 * kRrWaves - 1) / (64 * kRrWaves);
+    // weights: layer l, output block ob, step t, part, lane: thread tid takes
+    // (ob, t, lane) items tid + 512 u (at most 4 blocks x 8 steps x 64
+    // lanes), the 8 consecutive k steps of one weight row, two items'
+    // loads in flight before their LDS stores.  Each wave leaves a flag: a
+    // weight is outside the range of the split.
+    constexpr int kPer = 2;   // items per thread in flight
     auto stage = [&](int l0, int l1) {
+        bool huge = false;
         for (int l = l0; l < l1; ++l) {
-            const int K = a.dims[l], N = a.dims[l + 1];
-            const int ng = rr_steps(a.dims, l, a.k0h, a.cs) / 4;
-            const int total = rr_blocks(N) * ng * 64;
-            const unsigned inv = (65536u + ng - 1) / ng;   // gg / ng exactly for gg < 128
+            const int K = a.dims[l], N = a.dims[l + 1], nob = rr_blocks(N);
+            const int nt = rr_steps(a.dims, l, a.k0h);
+            const int total = nob * nt * 64;
+            const unsigned inv = nt > 0 ? (65536u + nt - 1) / nt : 0u;   // gg / nt exactly for gg < 128
             const float* __restrict__ W = a.W[l];
-            const bool wvec = (K % 4) == 0 && (reinterpret_cast<uintptr_t>(W) & 15) == 0;
-            float4 v[kPer];
+            // columns [base, end): a layer's inputs, or the first layer's
+            // wide source
+            const int base = l == 0 && a.cs > 0 ? a.ww : 0, end = l == 0 && a.cs > 0 ? base + K - a.cs : K;
+            float4* dn = smem4 + (a.woff[l] >> 2);
+            if (l == 0 && a.cs > 0 && tid < nob * 64) {
+                const int n = (tid >> 6) * 32 + (lane & 31), k = 4 * hk;
+                const float* wr = W + (int64_t)(n < N ? n : 0) * K + a.sw;
+                float q[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) q[e] = n < N && k + e < a.cs ? wr[k + e] : 0.0f;
+                dn[tid] = make_float4(q[0], q[1], q[2], q[3]);
+            }
+            uint4* dst = reinterpret_cast<uint4*>(dn) + rr_narrow_floats(nob, l, a.cs) / 4;
+            for (int i0 = tid; i0 < total + tid; i0 += 64 * kRrWaves * kPer) {
+            float v[kPer][8];
 #pragma unroll
             for (int u = 0; u < kPer; ++u) {
-                const int i = tid + 64 * kRrWaves * u;
+                const int i = i0 + 64 * kRrWaves * u;
                 const int ln = i & 63, gg = i >> 6;
-                const int ob = (int)(((unsigned)gg * inv) >> 16), g = gg - ob * ng;
+                const int ob = (int)(((unsigned)gg * inv) >> 16), t = gg - ob * nt;
                 const int n = ob * 32 + (ln & 31);
-                // columns k .. k + 3 of [base, end): a layer's inputs, or one
-                // of the first layer's two sources
-                const bool two = l == 0 && a.cs > 0, narrow = two && g == 0;
-                const int base = two ? (narrow ? a.sw : a.ww) : 0;
-                const int end = two ? base + (narrow ? a.cs : K - a.cs) : K;
-                const int k = base + (narrow ? 4 * (ln >> 5) : rr_k(l, 4 * (two ? g - 1 : g), ln >> 5));
-                v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (i < total && n < N) {
-                    const float* wr = W + (int64_t)n * K;
-                    if (wvec && !two && k + 4 <= K) {
-                        v[u] = *reinterpret_cast<const float4*>(wr + k);
-                    } else {
-                        v[u].x = k + 0 < end ? wr[k + 0] : 0.0f;
-                        v[u].y = k + 1 < end ? wr[k + 1] : 0.0f;
-                        v[u].z = k + 2 < end ? wr[k + 2] : 0.0f;
-                        v[u].w = k + 3 < end ? wr[k + 3] : 0.0f;
+                const float* wr = W + (int64_t)n * K;
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    const int k = base + rr_k(l, 8 * t + 4 * c, ln >> 5);
+                    float4 q = make_float4(0.f, 0.f, 0.f, 0.f);
+                    if (i < total && n < N) {
+                        if (k + 4 <= end) {
+                            // (global loads of 16 bytes take any 4-byte alignment)
+                            struct __attribute__((packed, aligned(4))) F4 { float x, y, z, w; };
+                            const F4 p = *reinterpret_cast<const F4*>(wr + k);
+                            q = make_float4(p.x, p.y, p.z, p.w);
+                        } else {
+                            q.x = k + 0 < end ? wr[k + 0] : 0.0f;
+                            q.y = k + 1 < end ? wr[k + 1] : 0.0f;
+                            q.z = k + 2 < end ? wr[k + 2] : 0.0f;
+                        }
                     }
+                    v[u][4 * c + 0] = q.x;
+                    v[u][4 * c + 1] = q.y;
+                    v[u][4 * c + 2] = q.z;
+                    v[u][4 * c + 3] = q.w;
                 }
             }
-            float4* dst = smem4 + (a.woff[l] >> 2);
 #pragma unroll
             for (int u = 0; u < kPer; ++u) {
-                const int i = tid + 64 * kRrWaves * u;
-                if (i < total) dst[i] = v[u];
+                const int i = i0 + 64 * kRrWaves * u;
+                if (i < total) {
+                    uint4 p[3];
+                    rr_split(v[u], p);
+                    bool out = false;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) out |= !(fabsf(v[u][e]) < kRrHuge);
+                    if (out) {
+                        huge = true;
+                        uint32_t w[3][8];
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) {
+                            uint32_t h[3];
+                            rr_split_huge(v[u][e], h);
+#pragma unroll
+                            for (int q = 0; q < 3; ++q) w[q][e] = h[q];
+                        }
+#pragma unroll
+                        for (int q = 0; q < 3; ++q)
+                            p[q] = make_uint4(w[q][0] | (w[q][1] << 16), w[q][2] | (w[q][3] << 16),
+                                              w[q][4] | (w[q][5] << 16), w[q][6] | (w[q][7] << 16));
+                    }
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) dst[((i >> 6) * 3 + q) * 64 + (i & 63)] = p[q];
+                }
+            }
             }
             const float* __restrict__ bs = a.bias[l];
-            for (int e = tid; e < rr_blocks(N) * 32; e += 64 * kRrWaves)
+            for (int e = tid; e < nob * 32; e += 64 * kRrWaves)
                 smem[a.boff[l] + e] = (bs && e < N) ? bs[e] : 0.0f;
         }
+        const bool any = __any(huge);
+        if (lane == 0) reinterpret_cast<int*>(smem)[a.foff + wave] = any;
+    };
+    bool plain_w = false;   // the staged weights need rr_products_plain
+    auto staged = [&]() {
+        __syncthreads();
+        int f = 0;
+#pragma unroll
+        for (int i = 0; i < kRrWaves; ++i) f |= reinterpret_cast<const int*>(smem)[a.foff + i];
+        plain_w = __builtin_amdgcn_readfirstlane(f) != 0;
     };
 
     // layer l on this wave's tile (rows row - lane % 32 ..): act in, act
@@ -377,12 +568,28 @@ void mlp_rr_kernel(RrArgs a) {
     auto layer = [&](int l, int64_t row, bool rok) {
         const int N = a.dims[l + 1];
         const int nob = rr_blocks(N);
-        const int ng = rr_steps(a.dims, l, a.k0h, a.cs) / 4;
-        const float4* __restrict__ wl = smem4 + (a.woff[l] >> 2) + lane;
+        const int nt = rr_steps(a.dims, l, a.k0h);
+        const float4* __restrict__ wn = smem4 + (a.woff[l] >> 2) + lane;
+        const uint4* __restrict__ wl = reinterpret_cast<const uint4*>(wn) + rr_narrow_floats(nob, l, a.cs) / 4;
         f32x16 acc[kRrMaxWidth / 32];
         const bool relu = (a.relu_mask >> l) & 1u;
-        // the sums start from the bias: VALU work that does not overlap the
-        // MFMAs is what this kernel loses
+#pragma unroll
+        for (int ob = 0; ob < kRrMaxWidth / 32; ++ob)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[ob][r] = 0.0f;
+        // the row's largest value (NaN apart, whose parts are NaN)
+        float top = 0.0f;
+#pragma unroll
+        for (int i = 0; i < kRrMaxSteps; i += 8)
+            if (i < 8 * nt)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) top = fmaxf(top, fabsf(act[i + e]));
+        if (plain_w || __any(!(top < kRrHuge) || (top < kRrSmall && top > 0.0f))) {
+            rr_products_plain(nt, nob, wl, act, acc);
+        } else {
+            if (nt > 0) rr_products(nt, nob, wl, act, acc);
+        }
+        if (l == 0 && a.cs > 0) rr_narrow(nob, wn, sm, acc);
         const float* __restrict__ bl = smem + a.boff[l] + 4 * hk;
 #pragma unroll
         for (int ob = 0; ob < kRrMaxWidth / 32; ++ob) {
@@ -390,23 +597,12 @@ void mlp_rr_kernel(RrArgs a) {
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const float4 b4 = *reinterpret_cast<const float4*>(bl + 32 * ob + 8 * q);
-                    acc[ob][4 * q + 0] = b4.x;
-                    acc[ob][4 * q + 1] = b4.y;
-                    acc[ob][4 * q + 2] = b4.z;
-                    acc[ob][4 * q + 3] = b4.w;
+                    acc[ob][4 * q + 0] += b4.x;
+                    acc[ob][4 * q + 1] += b4.y;
+                    acc[ob][4 * q + 2] += b4.z;
+                    acc[ob][4 * q + 3] += b4.w;
                 }
             }
-        }
-        if (l == 0 && a.cs > 0) {
-            rr_narrow(nob, wl, ng, sm, acc);
-            wl += 64;
-        }
-        switch (ng >> 2) {   // (the narrow source's group is the odd one)
-            case 0: break;
-            case 1: rr_products_nob<1>(nob, wl, ng, act, acc); break;
-            case 2: rr_products_nob<2>(nob, wl, ng, act, acc); break;
-            case 3: rr_products_nob<3>(nob, wl, ng, act, acc); break;
-            default: rr_products_nob<4>(nob, wl, ng, act, acc); break;
         }
         if (l + 1 < a.n_layers) {
             // the accumulators, activated, become the next layer's B operand
@@ -498,7 +694,7 @@ void mlp_rr_kernel(RrArgs a) {
 
     if constexpr (!PHASED) {
         stage(0, a.n_layers);
-        __syncthreads();
+        staged();
         for (int64_t t = t0; t < a.tiles; t += stride) {
             const int64_t row = t * 32 + (lane & 31);
             const bool rok = row < a.rows;
@@ -507,17 +703,21 @@ void mlp_rr_kernel(RrArgs a) {
         }
     } else {
         // the weights do not fit at once: the layers run in phases, the
-        // workgroup restaging the LDS between them, and each wave holds at
-        // most one tile (the host guarantees it), whose activations stay in
-        // registers across the phases.  Every wave takes every barrier.
-        const int64_t row = t0 * 32 + (lane & 31);
-        const bool rok = row < a.rows;
-        for (int p = 0; p < a.nphase; ++p) {
-            if (p > 0) __syncthreads();   // every wave is done with the previous phase's weights
-            stage(a.phase_first[p], a.phase_first[p + 1]);
-            __syncthreads();
-            if (t0 < a.tiles)
-                for (int l = a.phase_first[p]; l < a.phase_first[p + 1]; ++l) layer(l, row, rok);
+        // workgroup staging the LDS anew between them while the tiles'
+        // activations stay in registers; every wave takes every barrier,
+        // with or without a tile
+        for (int64_t w0 = t0 - wave; w0 < a.tiles; w0 += stride) {
+            const int64_t t = w0 + wave;
+            const int64_t row = t * 32 + (lane & 31);
+            const bool rok = row < a.rows;
+            if (t != t0 && t < a.tiles) load_tile(t, act);
+            for (int p = 0; p < a.nphase; ++p) {
+                __syncthreads();   // every wave is done with the previous phase's weights
+                stage(a.phase_first[p], a.phase_first[p + 1]);
+                staged();
+                if (t < a.tiles)
+                    for (int l = a.phase_first[p]; l < a.phase_first[p + 1]; ++l) layer(l, row, rok);
+            }
         }
     }
 }
@@ -525,7 +725,7 @@ void mlp_rr_kernel(RrArgs a) {
 struct RrPlan {
     bool ok;
     int k0h;
-    int lds_floats;
+    int lds_floats, foff;
     int woff[MESORASI_MAX_LAYERS], boff[MESORASI_MAX_LAYERS];
     int nphase;
     int phase_first[MESORASI_MAX_LAYERS + 1];
@@ -539,28 +739,34 @@ RrPlan rr_plan(int n_layers, const int32_t* dims, int cs) {
     if (n_layers < 1 || cs > 8 || cs > dims[0]) return p;
     p.k0h = (int)(ceil_div(ceil_div(dims[0] - cs, 2), 16) * 16);
     if (p.k0h > kRrMaxSteps) return p;
-    const int cap = kRrMaxLds / (int)sizeof(float);
+    const int cap = kRrMaxLds / (int)sizeof(float) - kRrWaves;   // (the waves' flags behind the weights)
     int off = 0, most = 0;
     p.nphase = 1;
     p.phase_first[0] = 0;
     for (int l = 0; l < n_layers; ++l) {
         if (dims[l + 1] > kRrMaxWidth || (l > 0 && dims[l] > kRrMaxWidth)) return p;
         const int nob = rr_blocks(dims[l + 1]);
-        const int size = nob * rr_steps(dims, l, p.k0h, cs) * 64 + nob * 32;
+        const int size = rr_floats(dims, l, p.k0h, cs);
         if (size > cap) return p;
         if (off + size > cap) {
             p.phase_first[p.nphase++] = l;
             off = 0;
         }
         p.woff[l] = off;
-        p.boff[l] = off + nob * rr_steps(dims, l, p.k0h, cs) * 64;
+        p.boff[l] = off + size - nob * 32;
         off += size;
         most = std::max(most, off);
     }
     p.phase_first[p.nphase] = n_layers;
-    p.lds_floats = most;
+    p.foff = most;
+    p.lds_floats = most + kRrWaves;
     p.ok = true;
     return p;
+}
+
+hipError_t rr_lds_attr(void (*kernel)(RrArgs)) {
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               kRrMaxLds);
 }
 
 int rr_cus() {
@@ -585,28 +791,34 @@ static int rr_narrow_source(const float* x0, int c0, int64_t ld0, const float* x
     return -1;
 }
 
-// One phase for any row count; several only while every wave holds at most
+// Any row count for layers of at most 160 KB of fp32 weights; with more, which
+// take three or more phases of staging, only while every wave holds at most
 // one 32-row tile (one persistent workgroup of kRrWaves waves per CU).
-static bool rr_rows_ok(const RrPlan& pl, int64_t rows) {
-    return pl.ok && (pl.nphase == 1 || ceil_div(rows, 32) <= (int64_t)rr_cus() * kRrWaves);
+static bool rr_rows_ok(int n_layers, const int32_t* dims, int cs, int64_t tiles_per_wave) {
+    const RrPlan pl = rr_plan(n_layers, dims, cs);
+    if (!pl.ok) return false;
+    int64_t bytes = 0;
+    for (int l = 0; l < n_layers; ++l)
+        bytes += rr_blocks(dims[l + 1]) * (rr_steps(dims, l, pl.k0h) * 2048 + (l == 0 && cs > 0 ? 1024 : 0) + 128);
+    return bytes <= kRrMaxLds || tiles_per_wave <= 1;
 }
+static int64_t rr_tiles_per_wave(int64_t rows) { return ceil_div(ceil_div(rows, 32), (int64_t)rr_cus() * kRrWaves); }
 
 bool rr_mlp_supported(int n_layers, const int32_t* dims, int64_t rows) {
-    return dims[0] <= kRrMaxWidth && rr_rows_ok(rr_plan(n_layers, dims, 0), rows);
+    return dims[0] <= kRrMaxWidth && rr_rows_ok(n_layers, dims, 0, rr_tiles_per_wave(rows));
 }
 
 bool rr_mlp_supported(const float* x0, int c0, int64_t ld0, const float* x1, int c1, int64_t ld1, int n_layers,
                       const int32_t* dims, int64_t rows) {
     const int narrow = rr_narrow_source(x0, c0, ld0, x1, c1, ld1);
     if (narrow < 0) return rr_mlp_supported(n_layers, dims, rows);
-    return rr_rows_ok(rr_plan(n_layers, dims, narrow == 2 ? dims[0] : narrow == 0 ? c0 : c1), rows);
+    return rr_rows_ok(n_layers, dims, narrow == 2 ? dims[0] : narrow == 0 ? c0 : c1, rr_tiles_per_wave(rows));
 }
 
 bool rr_pool_supported(int cf, const float* feat, int64_t ld_f, int n_layers, const int32_t* dims, int K) {
     if (K != 16 && K != 32) return false;
     if (cf > 0 && (cf % 4 != 0 || ld_f % 4 != 0 || !aligned(feat, 16))) return false;
-    const RrPlan pl = rr_plan(n_layers, dims, 3);
-    return pl.ok && pl.nphase == 1;
+    return rr_rows_ok(n_layers, dims, 3, 2);
 }
 
 int run_rr_mlp(const float* x0, int c0, int64_t ld0, const float* x1, int c1, int64_t ld1, int64_t rows,
@@ -618,15 +830,11 @@ int run_rr_mlp(const float* x0, int c0, int64_t ld0, const float* x1, int c1, in
     MESO_REQUIRE(pl.ok, MESORASI_EUNSUPPORTED, "mesorasi_pointwise_mlp: layers too wide for the register MLP");
     if (rows == 0) return MESORASI_OK;
     const int cus = rr_cus();
-    MESO_REQUIRE(rr_rows_ok(pl, rows) && (!g || pl.nphase == 1), MESORASI_EUNSUPPORTED,
-                 "mesorasi_pointwise_mlp: staged register MLP on more than one tile per wave");
-    static const hipError_t attr[3] = {
-        hipFuncSetAttribute(reinterpret_cast<const void*>(&mlp_rr_kernel<false, false>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, kRrMaxLds),
-        hipFuncSetAttribute(reinterpret_cast<const void*>(&mlp_rr_kernel<true, false>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, kRrMaxLds),
-        hipFuncSetAttribute(reinterpret_cast<const void*>(&mlp_rr_kernel<false, true>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, kRrMaxLds)};
+    static const auto kernels = std::array<void (*)(RrArgs), 4>{
+        &mlp_rr_kernel<false, false>, &mlp_rr_kernel<false, true>, &mlp_rr_kernel<true, false>,
+        &mlp_rr_kernel<true, true>};
+    static const hipError_t attr[4] = {rr_lds_attr(kernels[0]), rr_lds_attr(kernels[1]), rr_lds_attr(kernels[2]),
+                                       rr_lds_attr(kernels[3])};
     for (const hipError_t e : attr)
         MESO_REQUIRE(e == hipSuccess, MESORASI_EHIP, "mesorasi_pointwise_mlp: LDS size attribute: %s",
                      hipGetErrorString(e));
@@ -665,7 +873,7 @@ int run_rr_mlp(const float* x0, int c0, int64_t ld0, const float* x1, int c1, in
         a.woff[l] = pl.woff[l];
         a.boff[l] = pl.boff[l];
     }
-    a.lds_floats = pl.lds_floats;
+    a.foff = pl.foff;
     a.nphase = pl.nphase;
     for (int q = 0; q <= pl.nphase; ++q) a.phase_first[q] = pl.phase_first[q];
     a.relu_mask = relu_mask;
@@ -686,9 +894,7 @@ int run_rr_mlp(const float* x0, int c0, int64_t ld0, const float* x1, int c1, in
     int64_t grid = std::min<int64_t>(ceil_div(a.tiles, kRrWaves), cus);
     if ((a.interp || g) && 8 * ceil_div(grid, 8) <= cus) grid = 8 * ceil_div(grid, 8);
     const size_t lds = (size_t)pl.lds_floats * sizeof(float);
-    if (g) mlp_rr_kernel<false, true><<<dim3((unsigned)grid), dim3(64 * kRrWaves), lds, s>>>(a);
-    else if (pl.nphase > 1) mlp_rr_kernel<true, false><<<dim3((unsigned)grid), dim3(64 * kRrWaves), lds, s>>>(a);
-    else mlp_rr_kernel<false, false><<<dim3((unsigned)grid), dim3(64 * kRrWaves), lds, s>>>(a);
+    kernels[(pl.nphase > 1 ? 2 : 0) + (g ? 1 : 0)]<<<dim3((unsigned)grid), dim3(64 * kRrWaves), lds, s>>>(a);
     return after_launch("mesorasi_pointwise_mlp (register MLP)");
 }
 

@@ -522,6 +522,38 @@ def test_mlp_parity(gpu, name, rows, srcs, widths, dt):
         assert np.array_equal(host(yb.float()), host(y))
 
 
+@pytest.mark.parametrize("where,value", [("x", 3.0e38), ("x", np.inf), ("x", np.nan), ("w", 3.0e38), ("w", -np.inf),
+                                         ("all_x", 1e-30)])
+def test_mlp_register_split_range(gpu, where, value):
+    """Values that three bf16 parts cannot hold exactly (huge, infinite, very
+    small): the register MLP's result is that of fp32 products -- finite,
+    infinite and NaN in the same places as the fp64 product rounded to fp32,
+    within the rounding of 64 fp32 sums where finite."""
+    rr = g(31)
+    rows, dims = 32800, [64, 96]
+    x = rr.standard_normal((rows, dims[0])).astype(np.float32)
+    W = (rr.standard_normal((dims[1], dims[0])) / 8).astype(np.float32)
+    b = np.zeros(dims[1], np.float32)
+    W[:, 5] = np.where(np.abs(W[:, 5]) < 1e-3, 1e-3, W[:, 5])   # (no 0 x inf)
+    if where == "x":
+        x[[3, 777, 32799], 5] = value
+    elif where == "w":
+        x = np.abs(x) + np.float32(0.5)
+        x[:, 7] *= np.float32(0.01)
+        W[[2, 95], 7] = value
+    else:
+        x = (x * np.float32(value)).astype(np.float32)
+    y = host(ops.pointwise_mlp(dev(x), ops.MLPParams([W], [b]), relu_mask=0))
+    with np.errstate(over="ignore", invalid="ignore"):
+        ref = (x.astype(np.float64) @ W.T.astype(np.float64)).astype(np.float32)
+    assert np.array_equal(np.isnan(y), np.isnan(ref)) and np.array_equal(np.isinf(y), np.isinf(ref))
+    ok = np.isfinite(ref)
+    # the sum of 64 fp32 products and its rounding: 64 x 2^-24 of the largest term at most
+    with np.errstate(over="ignore", invalid="ignore"):
+        big = np.abs(x.astype(np.float64)) @ np.abs(W.T.astype(np.float64))
+    assert np.all(np.abs(y[ok].astype(np.float64) - ref[ok]) <= 64 * 2.0 ** -24 * big[ok])
+
+
 @pytest.mark.parametrize("dt", [F32, BF16])
 @pytest.mark.parametrize("G", [128, 20, 64, 1])
 def test_mlp_pooled(gpu, dt, G):

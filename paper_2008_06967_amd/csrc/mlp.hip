@@ -906,22 +906,28 @@ static bool use_fused(int64_t rows, int n_layers, const int32_t* dims, int dtype
     return fused_mlp_supported(n_layers, dims, dtype) && (neighbor_rows || rows <= kFusedMaxPlainRows);
 }
 
-// The register-resident MLP (mlp_rr.hip, mlp_rr_bf16.hip) for plain rows
-// above that count when every layer is at most 128 wide; in bf16 only for
-// first layers of at most 32 inputs, where the GEMM's per-layer launches
-// and HBM round trips dominate (65536 x 3 -> 32 -> 32 -> 64: 16.6 against
-// 20.8 us); on 128-wide rows the bf16 GEMM is faster (65536 x 128 -> 128
-// -> 128: 28.5 against 34.7 us), its MFMA work being a sixteenth of fp32's.
-// A first layer of a wide and a narrow source (65536 x 131 -> 128 -> 128 ->
-// 128) takes it too: 80 us against 100 for the GEMM layers.
+// The register-resident MLP (mlp_rr.hip, mlp_rr_bf16.hip) for plain rows.
+// fp32: above that count when every layer is at most 128 wide (65536 x 131 ->
+// 128 -> 128 -> 128: 57 us against 100 for the GEMM layers).
+// bf16: the GEMM's launches and HBM round trips per layer dominate.  Up to 96
+// KB of weights, staged by every workgroup, it wins from 1024 rows on (1024 x
+// 131 -> 64 -> 64 -> 128: 17.2 against 21.0 us; 65536 rows: 24 against 43);
+// with more, only from many rows on (131 -> 128 -> 128 -> 256: 4096 rows 27.3
+// against 21.4, 32768 rows 30.8 against 41.2, 65536 rows 36 against 62; at
+// 16384 rows 3 -> 128 -> 128 -> 256 still loses, 22.5 against 20.7).
 constexpr int64_t kRrMinRows = kFusedMaxPlainRows + 1;
+constexpr int64_t kRbMinRows = 1024, kRbMinRowsWide = 16385;
+constexpr int kRbFewWeights = 98 * 1024;   // (96 KB and the biases)
 static bool use_rr(const float* x0, int c0, int64_t ld0, const float* x1, int c1, int64_t ld1, int64_t rows,
                    int n_layers, const int32_t* dims, int dtype, int out_dtype, int64_t pool_group,
                    bool neighbor_rows) {
-    if (pool_group != 0 || neighbor_rows || rows < kRrMinRows) return false;
+    if (pool_group != 0 || neighbor_rows) return false;
     if (dtype == MESORASI_F32)
-        return out_dtype == MESORASI_F32 && rr_mlp_supported(x0, c0, ld0, x1, c1, ld1, n_layers, dims, rows);
-    return dtype == MESORASI_BF16 && dims[0] <= 32 && rb_mlp_supported(n_layers, dims);
+        return rows >= kRrMinRows && out_dtype == MESORASI_F32 &&
+               rr_mlp_supported(x0, c0, ld0, x1, c1, ld1, n_layers, dims, rows);
+    if (dtype != MESORASI_BF16 || rows < kRbMinRows || n_layers < 2) return false;
+    const int lds = rb_mlp_lds_bytes(x0, c0, ld0, x1, c1, ld1, n_layers, dims);
+    return lds > 0 && (lds <= kRbFewWeights || rows >= kRbMinRowsWide);
 }
 
 // Gathered neighbor rows pooled over 16 or 32 of them take the register MLP

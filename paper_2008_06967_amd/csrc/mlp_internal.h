@@ -81,9 +81,14 @@ int run_rr_mlp(const float* x0, int c0, int64_t ld0, const float* x1, int c1, in
                uint32_t relu_mask, float* y, int64_t ld_y, hipStream_t s, const RrInterp* ip = nullptr,
                const MlpGather* g = nullptr);
 
-// The same for bf16 MLPs (mlp_rr_bf16.hip): every layer at most 128 wide;
-// fp32 rows in, fp32 or bf16 y out (bf16-rounded values either way).
-bool rb_mlp_supported(int n_layers, const int32_t* dims);
+// The same for bf16 MLPs (mlp_rr_bf16.hip): hidden layers at most 128 wide,
+// the output at most 256, the weights in the LDS of one workgroup together;
+// the first layer an aligned source of at most 128 channels, one of at most 8
+// beside it, or any sources of at most 32; fp32 rows in, fp32 or bf16 y out
+// (bf16-rounded values either way).  Returns the LDS of a workgroup (weights
+// and biases), 0 where it does not apply.
+int rb_mlp_lds_bytes(const float* x0, int c0, int64_t ld0, const float* x1, int c1, int64_t ld1, int n_layers,
+                     const int32_t* dims);
 int run_rb_mlp(const float* x0, int c0, int64_t ld0, const float* x1, int c1, int64_t ld1, int64_t rows,
                int n_layers, const int32_t* dims, const void* const* W, const float* const* bias,
                uint32_t relu_mask, int out_dtype, void* y, int64_t ld_y, hipStream_t s);

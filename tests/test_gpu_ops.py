@@ -494,6 +494,12 @@ MLP_CASES = [
     ("rr_bf16_wide_ragged", 40001, [32], [128, 128, 13], BF16),
     ("rr_bf16_odd_widths", 33001, [5, 2], [33, 17, 9], BF16),
     ("rr_bf16_depth_max", 32769, [16], [32] * 8, BF16),
+    # a wide first layer (alone or beside a narrow one), up to 256 outputs,
+    # few rows spread over the CUs
+    ("rr_bf16_narrow_first", 40001, [3, 128], [128, 128, 256], BF16),
+    ("rr_bf16_narrow_last", 2049, [36, 7], [100, 129], BF16),
+    ("rr_bf16_wide_odd_out", 1025, [128], [64, 161], BF16),
+    ("rr_bf16_lds_limit", 4096, [8, 64], [128, 128, 128, 256], BF16),
 ]
 
 

@@ -459,9 +459,9 @@ def interpolate3_add(nit: torch.Tensor, dist: torch.Tensor, f_src: torch.Tensor,
 def interpolate3_mlp_supported(p: MLPParams, rows: int) -> bool:
     """mesorasi_interpolate3_mlp applies: an fp32 MLP whose layers are all at
     most 128 wide (the register-resident MLP), first layer a multiple of 4,
-    and, when the layers' permuted weights do not fit 160 KB of LDS
-    together, at most one 32-row tile per wave (8 per compute unit).  This
-    mirrors the library's plan."""
+    and, when the layers' fp32 weights make more than 160 KB, at most one
+    32-row tile per wave (8 per compute unit).  This mirrors the library's
+    rule."""
     if p.dtype != F32 or p.dims[0] % 4 != 0 or any(d > 128 for d in p.dims):
         return False
     h0 = ((p.dims[0] + 1) // 2 + 15) // 16 * 16     # first-layer k steps, as the library pads them

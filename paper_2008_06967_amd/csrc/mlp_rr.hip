@@ -28,10 +28,12 @@
 // The three products left out are below 2^-25 of the product together, less
 // than the rounding of one fp32 sum, and there are fewer of those (six per
 // 16 k instead of sixteen).  The parts of huge values would overflow, those of
-// infinities would be NaN and those of very small ones denormal, so a tile
-// whose weights or activations hold such values is multiplied by
-// v_mfma_f32_32x32x2_f32 on the same operands, the weights put together
-// again (rr_products_plain).
+// infinities would be NaN and those of very small ones denormal, and products
+// that overflow would meet others of the opposite sign.  So the weights and
+// each row's largest value are tested against a range in which none of this
+// occurs (kRrSmall).  Weights with one outside it are staged again as fp32 and
+// multiplied by v_mfma_f32_32x32x2_f32; so are the rows of a tile with one
+// outside it, by the weights' parts put together again (rr_products_plain).
 // Measured: 524288 gathered rows 3 -> 64 -> 64 -> 128, pooled: 128 -> 103 us;
 // 65536 x 131 -> 128 -> 128 -> 128: 77 -> 57 us with its launch; error against
 // 64 bits 1.3e-7 -> 7e-8 and 2.8e-7 -> 1.2e-7 (2-norm).  What bounds it now is
@@ -66,7 +68,11 @@ constexpr int kRrWaves = 8;          // waves per workgroup (two per SIMD)
 constexpr int kRrMaxWidth = 128;     // widest layer input or output
 constexpr int kRrMaxSteps = 64;      // k steps of a layer (128 inputs / 2)
 constexpr int kRrMaxLds = 160 * 1024;
-constexpr float kRrHuge = 0x1p120f, kRrSmall = 0x1p-80f;   // the range in which the bf16 parts are exact
+// The split takes weights that are 0 or in [2^-50, 2^20) and a row whose
+// largest value is 0 or in [2^-50, 2^96), so that every product, part and sum
+// of 136 is finite.  (A value below 2^-103 beside larger ones of its row has
+// parts that are not normal: an output is off by less than 2^-97 by it.)
+constexpr float kRrSmall = 0x1p-50f, kRrMaxW = 0x1p20f, kRrMaxX = 0x1p96f;
 
 struct RrArgs {
     const float* x0;
@@ -82,7 +88,7 @@ struct RrArgs {
     const float* bias[MESORASI_MAX_LAYERS];
     int woff[MESORASI_MAX_LAYERS];   // float offset of layer l's permuted weights in LDS
     int boff[MESORASI_MAX_LAYERS];   // float offset of its padded bias
-    int foff;                        // int offset of the waves' flags (a weight out of the split's range)
+    int foff;                        // int offset of the waves' flags (a weight outside the split's range)
     // weights staged in phases when all layers do not fit at once: phase p
     // holds layers phase_first[p] .. phase_first[p + 1] - 1 (offsets above
     // relative to the phase)
@@ -165,22 +171,6 @@ __device__ __forceinline__ void rr_split(const float* v, uint4 (&p)[3]) {
     }
 #pragma unroll
     for (int q = 0; q < 3; ++q) p[q] = make_uint4(w[q][0], w[q][1], w[q][2], w[q][3]);
-}
-
-// One weight outside the range of rr_split: parts that sum to it exactly,
-// none of them rounded up to infinity.
-__device__ __forceinline__ void rr_split_huge(float v, uint32_t (&p)[3]) {
-    p[1] = p[2] = 0;
-    if (v != v) p[0] = 0x7fc0u;
-    else {
-        const uint32_t u = __float_as_uint(v);
-        p[0] = u >> 16;
-        if ((u & 0x7f800000u) == 0x7f800000u) return;
-        const float r = v - __uint_as_float(u & 0xffff0000u);
-        const uint32_t ur = __float_as_uint(r);
-        p[1] = ur >> 16;
-        p[2] = __float_as_uint(r - __uint_as_float(ur & 0xffff0000u)) >> 16;
-    }
 }
 
 __device__ __forceinline__ bf16x8 rr_bf16x8(uint4 v) { return __builtin_bit_cast(bf16x8, v); }
@@ -268,8 +258,28 @@ __device__ __forceinline__ void rr_products(int nt, int nob, const uint4* __rest
     }
 }
 
-// The same products on the fp32 instruction, for values outside the range of
-// rr_split (not a path that sizes or ordinary values reach).
+// The same products on the fp32 instruction, the weights staged as fp32: two
+// float4 (8 k) per lane and step.
+__device__ __forceinline__ void rr_products_f32(int nt, int nob, const float4* __restrict__ wl,
+                                                const float (&act)[kRrMaxSteps], f32x16 (&acc)[kRrMaxWidth / 32]) {
+#pragma unroll
+    for (int t = 0; t < kRrMaxSteps / 8; ++t) {
+        if (t < nt) {
+#pragma unroll
+            for (int ob = 0; ob < kRrMaxWidth / 32; ++ob) {
+                if (ob < nob) {
+                    const float4 u = wl[(ob * nt + t) * 128], v = wl[(ob * nt + t) * 128 + 64];
+                    const float w[8] = {u.x, u.y, u.z, u.w, v.x, v.y, v.z, v.w};
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        acc[ob] = __builtin_amdgcn_mfma_f32_32x32x2f32(w[e], act[8 * t + e], acc[ob], 0, 0, 0);
+                }
+            }
+        }
+    }
+}
+
+// The same on the weights' parts, for rows outside the range of rr_split.
 __device__ __forceinline__ void rr_products_plain(int nt, int nob, const uint4* __restrict__ wl,
                                                   const float (&act)[kRrMaxSteps], f32x16 (&acc)[kRrMaxWidth / 32]) {
 #pragma unroll
@@ -466,8 +476,8 @@ void mlp_rr_kernel(RrArgs a) {
     // loads in flight before their LDS stores.  Each wave leaves a flag: a
     // weight is outside the range of the split.
     constexpr int kPer = 2;   // items per thread in flight
-    auto stage = [&](int l0, int l1) {
-        bool huge = false;
+    auto stage = [&](int l0, int l1, bool plain) {
+        bool outside = false;
         for (int l = l0; l < l1; ++l) {
             const int K = a.dims[l], N = a.dims[l + 1], nob = rr_blocks(N);
             const int nt = rr_steps(a.dims, l, a.k0h);
@@ -486,81 +496,86 @@ void mlp_rr_kernel(RrArgs a) {
                 for (int e = 0; e < 4; ++e) q[e] = n < N && k + e < a.cs ? wr[k + e] : 0.0f;
                 dn[tid] = make_float4(q[0], q[1], q[2], q[3]);
             }
-            uint4* dst = reinterpret_cast<uint4*>(dn) + rr_narrow_floats(nob, l, a.cs) / 4;
+            dn += rr_narrow_floats(nob, l, a.cs) / 4;
+            uint4* dst = reinterpret_cast<uint4*>(dn);
             for (int i0 = tid; i0 < total + tid; i0 += 64 * kRrWaves * kPer) {
-            float v[kPer][8];
+                float v[kPer][8];
 #pragma unroll
-            for (int u = 0; u < kPer; ++u) {
-                const int i = i0 + 64 * kRrWaves * u;
-                const int ln = i & 63, gg = i >> 6;
-                const int ob = (int)(((unsigned)gg * inv) >> 16), t = gg - ob * nt;
-                const int n = ob * 32 + (ln & 31);
-                const float* wr = W + (int64_t)n * K;
+                for (int u = 0; u < kPer; ++u) {
+                    const int i = i0 + 64 * kRrWaves * u;
+                    const int ln = i & 63, gg = i >> 6;
+                    const int ob = (int)(((unsigned)gg * inv) >> 16), t = gg - ob * nt;
+                    const int n = ob * 32 + (ln & 31);
+                    const float* wr = W + (int64_t)n * K;
 #pragma unroll
-                for (int c = 0; c < 2; ++c) {
-                    const int k = base + rr_k(l, 8 * t + 4 * c, ln >> 5);
-                    float4 q = make_float4(0.f, 0.f, 0.f, 0.f);
-                    if (i < total && n < N) {
-                        if (k + 4 <= end) {
-                            // (global loads of 16 bytes take any 4-byte alignment)
-                            struct __attribute__((packed, aligned(4))) F4 { float x, y, z, w; };
-                            const F4 p = *reinterpret_cast<const F4*>(wr + k);
-                            q = make_float4(p.x, p.y, p.z, p.w);
-                        } else {
-                            q.x = k + 0 < end ? wr[k + 0] : 0.0f;
-                            q.y = k + 1 < end ? wr[k + 1] : 0.0f;
-                            q.z = k + 2 < end ? wr[k + 2] : 0.0f;
+                    for (int c = 0; c < 2; ++c) {
+                        const int k = base + rr_k(l, 8 * t + 4 * c, ln >> 5);
+                        float4 q = make_float4(0.f, 0.f, 0.f, 0.f);
+                        if (i < total && n < N) {
+                            if (k + 4 <= end) {
+                                // (global loads of 16 bytes take any 4-byte alignment)
+                                struct __attribute__((packed, aligned(4))) F4 { float x, y, z, w; };
+                                const F4 p = *reinterpret_cast<const F4*>(wr + k);
+                                q = make_float4(p.x, p.y, p.z, p.w);
+                            } else {
+                                q.x = k + 0 < end ? wr[k + 0] : 0.0f;
+                                q.y = k + 1 < end ? wr[k + 1] : 0.0f;
+                                q.z = k + 2 < end ? wr[k + 2] : 0.0f;
+                            }
                         }
+                        v[u][4 * c + 0] = q.x;
+                        v[u][4 * c + 1] = q.y;
+                        v[u][4 * c + 2] = q.z;
+                        v[u][4 * c + 3] = q.w;
                     }
-                    v[u][4 * c + 0] = q.x;
-                    v[u][4 * c + 1] = q.y;
-                    v[u][4 * c + 2] = q.z;
-                    v[u][4 * c + 3] = q.w;
                 }
-            }
 #pragma unroll
-            for (int u = 0; u < kPer; ++u) {
-                const int i = i0 + 64 * kRrWaves * u;
-                if (i < total) {
-                    uint4 p[3];
-                    rr_split(v[u], p);
-                    bool out = false;
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) out |= !(fabsf(v[u][e]) < kRrHuge);
-                    if (out) {
-                        huge = true;
-                        uint32_t w[3][8];
+                for (int u = 0; u < kPer; ++u) {
+                    const int i = i0 + 64 * kRrWaves * u;
+                    if (i < total) {
+                        if (plain) {
+                            float4* d = dn + (i >> 6) * 128 + (i & 63);
+                            d[0] = make_float4(v[u][0], v[u][1], v[u][2], v[u][3]);
+                            d[64] = make_float4(v[u][4], v[u][5], v[u][6], v[u][7]);
+                            continue;
+                        }
+                        // (the smallest by its bits doubled, less one, which
+                        // puts 0 last; a NaN is above the range)
+                        unsigned most = 0, least = ~0u;
 #pragma unroll
                         for (int e = 0; e < 8; ++e) {
-                            uint32_t h[3];
-                            rr_split_huge(v[u][e], h);
-#pragma unroll
-                            for (int q = 0; q < 3; ++q) w[q][e] = h[q];
+                            const unsigned d = __float_as_uint(v[u][e]) << 1;
+                            most = max(most, d);
+                            least = min(least, d - 1);
                         }
+                        outside |= most >= __float_as_uint(kRrMaxW) << 1 || least < (__float_as_uint(kRrSmall) << 1) - 1;
+                        uint4 p[3];
+                        rr_split(v[u], p);
 #pragma unroll
-                        for (int q = 0; q < 3; ++q)
-                            p[q] = make_uint4(w[q][0] | (w[q][1] << 16), w[q][2] | (w[q][3] << 16),
-                                              w[q][4] | (w[q][5] << 16), w[q][6] | (w[q][7] << 16));
+                        for (int q = 0; q < 3; ++q) dst[((i >> 6) * 3 + q) * 64 + (i & 63)] = p[q];
                     }
-#pragma unroll
-                    for (int q = 0; q < 3; ++q) dst[((i >> 6) * 3 + q) * 64 + (i & 63)] = p[q];
                 }
-            }
             }
             const float* __restrict__ bs = a.bias[l];
             for (int e = tid; e < nob * 32; e += 64 * kRrWaves)
                 smem[a.boff[l] + e] = (bs && e < N) ? bs[e] : 0.0f;
         }
-        const bool any = __any(huge);
+        if (plain) return;
+        const bool any = __any(outside);
         if (lane == 0) reinterpret_cast<int*>(smem)[a.foff + wave] = any;
     };
-    bool plain_w = false;   // the staged weights need rr_products_plain
-    auto staged = [&]() {
+    bool plain_w = false;   // the staged weights are fp32
+    auto stage_phase = [&](int l0, int l1) {
+        stage(l0, l1, false);
         __syncthreads();
         int f = 0;
 #pragma unroll
         for (int i = 0; i < kRrWaves; ++i) f |= reinterpret_cast<const int*>(smem)[a.foff + i];
         plain_w = __builtin_amdgcn_readfirstlane(f) != 0;
+        if (plain_w) {
+            stage(l0, l1, true);
+            __syncthreads();
+        }
     };
 
     // layer l on this wave's tile (rows row - lane % 32 ..): act in, act
@@ -577,17 +592,19 @@ void mlp_rr_kernel(RrArgs a) {
         for (int ob = 0; ob < kRrMaxWidth / 32; ++ob)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[ob][r] = 0.0f;
-        // the row's largest value (NaN apart, whose parts are NaN)
-        float top = 0.0f;
-#pragma unroll
-        for (int i = 0; i < kRrMaxSteps; i += 8)
-            if (i < 8 * nt)
-#pragma unroll
-                for (int e = 0; e < 8; ++e) top = fmaxf(top, fabsf(act[i + e]));
-        if (plain_w || __any(!(top < kRrHuge) || (top < kRrSmall && top > 0.0f))) {
-            rr_products_plain(nt, nob, wl, act, acc);
+        if (plain_w) {
+            rr_products_f32(nt, nob, reinterpret_cast<const float4*>(wl), act, acc);
         } else {
-            if (nt > 0) rr_products(nt, nob, wl, act, acc);
+            // the row's largest value (NaN apart, whose parts are NaN)
+            float top = 0.0f;
+#pragma unroll
+            for (int i = 0; i < kRrMaxSteps; i += 8)
+                if (i < 8 * nt)
+#pragma unroll
+                    for (int e = 0; e < 8; e += 2)
+                        asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(top) : "v"(act[i + e]), "v"(act[i + e + 1]));
+            if (__any(!(top < kRrMaxX) || (top < kRrSmall && top > 0.0f))) rr_products_plain(nt, nob, wl, act, acc);
+            else if (nt > 0) rr_products(nt, nob, wl, act, acc);
         }
         if (l == 0 && a.cs > 0) rr_narrow(nob, wn, sm, acc);
         const float* __restrict__ bl = smem + a.boff[l] + 4 * hk;
@@ -693,8 +710,7 @@ void mlp_rr_kernel(RrArgs a) {
     };
 
     if constexpr (!PHASED) {
-        stage(0, a.n_layers);
-        staged();
+        stage_phase(0, a.n_layers);
         for (int64_t t = t0; t < a.tiles; t += stride) {
             const int64_t row = t * 32 + (lane & 31);
             const bool rok = row < a.rows;
@@ -713,8 +729,7 @@ void mlp_rr_kernel(RrArgs a) {
             if (t != t0 && t < a.tiles) load_tile(t, act);
             for (int p = 0; p < a.nphase; ++p) {
                 __syncthreads();   // every wave is done with the previous phase's weights
-                stage(a.phase_first[p], a.phase_first[p + 1]);
-                staged();
+                stage_phase(a.phase_first[p], a.phase_first[p + 1]);
                 if (t < a.tiles)
                     for (int l = a.phase_first[p]; l < a.phase_first[p + 1]; ++l) layer(l, row, rok);
             }

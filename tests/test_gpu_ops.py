@@ -560,6 +560,54 @@ def test_mlp_register_split_range(gpu, where, value):
     assert np.all(np.abs(y[ok].astype(np.float64) - ref[ok]) <= 64 * 2.0 ** -24 * big[ok])
 
 
+# (name, |x|, |w|): one nonzero channel per row, so that an output is one
+# product.  Each operand of these is an ordinary fp32 value; the product, or
+# the bf16 parts of an operand, leave the normal range.
+PRODUCT_RANGE = [
+    ("inf_2p68", 2.0 ** 68, 2.0 ** 68),
+    ("inf_2p70", 1.7 * 2.0 ** 70, 1.3 * 2.0 ** 70),
+    ("inf_parts_below", 1.255 * 2.0 ** 73, 1.255 * 2.0 ** 73),   # both second parts negative
+    ("inf_2p100", 1.003 * 2.0 ** 100, 2.0 ** 40),
+    ("largest_finite", 2.0 ** 64 * (1 - 2.0 ** -10), 2.0 ** 64 * (1 - 2.0 ** -10)),   # both first parts round up
+    ("x_edge", 2.0 ** 96 * (1 - 2.0 ** -24), 2.0 ** 20 * (1 - 2.0 ** -24)),
+    ("w_edge", 2.0 ** 96, 2.0 ** -50),
+    ("w_edge_outside", 2.0 ** 30, 2.0 ** -50 * (1 - 2.0 ** -24)),
+    ("small_w", 2.0 ** 50, 1.2345678 * 2.0 ** -115),             # w's third part below 2^-133
+    ("small_x", 1.2345678 * 2.0 ** -115, 2.0 ** 50),
+    ("small_x_beside", 1.2345678 * 2.0 ** -115, 2.0 ** 19),      # x's parts, below 2^-97 of an output
+    ("ordinary", 1.0 + 2.0 ** -8 - 2.0 ** -17, 1.0 + 2.0 ** -8 - 2.0 ** -17),   # the omitted parts at their largest
+]
+
+
+@pytest.mark.parametrize("relu", [0, 1])
+@pytest.mark.parametrize("name,xv,wv", PRODUCT_RANGE, ids=[c[0] for c in PRODUCT_RANGE])
+def test_mlp_register_product_range(gpu, name, xv, wv, relu):
+    """The register MLP on products at the ends of fp32's range: infinite
+    where the fp32 product is, finite elsewhere and within 2^-23 of it (half
+    for the rounding, half for what the split omits) and 2^-97 (parts of a
+    value that are not normal beside an ordinary one, which here meets zero
+    weights)."""
+    rr = g(33)
+    rows, K, N = 32800, 64, 96
+    xv, wv = np.float32(xv), np.float32(wv)
+    x = np.zeros((rows, K), np.float32)
+    ch = 1 + rr.integers(0, K - 1, rows)
+    x[np.arange(rows), ch] = xv * rr.choice(np.array([-1.0, 1.0], np.float32), rows)
+    x[:, 0] = 1.0
+    W = wv * rr.choice(np.array([-1.0, 1.0], np.float32), (N, K))
+    W[:, 0] = 0.0
+    ref = x[np.arange(rows), ch][:, None].astype(np.float64) * W[:, ch].T.astype(np.float64)
+    if relu:
+        ref = np.maximum(ref, 0.0)
+    y = host(ops.pointwise_mlp(dev(x), ops.MLPParams([W], [np.zeros(N, np.float32)]), relu_mask=relu)).astype(np.float64)
+    with np.errstate(over="ignore"):
+        r32 = ref.astype(np.float32).astype(np.float64)
+    inf = np.isinf(r32)
+    assert inf.any() == name.startswith("inf")
+    assert np.array_equal(y[inf], r32[inf])
+    assert np.all(np.abs(y[~inf] - ref[~inf]) <= 2.0 ** -23 * np.abs(ref[~inf]) + 2.0 ** -97)
+
+
 @pytest.mark.parametrize("dt", [F32, BF16])
 @pytest.mark.parametrize("G", [128, 20, 64, 1])
 def test_mlp_pooled(gpu, dt, G):

@@ -260,8 +260,8 @@ __device__ __forceinline__ void rr_products(int nt, int nob, const uint4* __rest
 
 // The same products on the fp32 instruction, the weights staged as fp32: two
 // float4 (8 k) per lane and step.
-__device__ __forceinline__ void rr_products_f32(int nt, int nob, const float4* __restrict__ wl,
-                                                const float (&act)[kRrMaxSteps], f32x16 (&acc)[kRrMaxWidth / 32]) {
+__device__ __forceinline__ void rr_products_f32_any(int nt, int nob, const float4* __restrict__ wl,
+                                                    const float (&act)[kRrMaxSteps], f32x16 (&acc)[kRrMaxWidth / 32]) {
 #pragma unroll
     for (int t = 0; t < kRrMaxSteps / 8; ++t) {
         if (t < nt) {
@@ -325,6 +325,80 @@ __device__ __forceinline__ float rr_relu(float v) {
     return r;
 }
 
+// One tile's layer-0 input but for a narrow source: the lane's row, step s
+// taking channel kb + 8 (s / 4) + s % 4.
+__device__ __forceinline__ void rr_load_rows(const RrArgs& a, int64_t row, bool rok, int kb,
+                                             float (&dst)[kRrMaxSteps]) {
+            if (a.interp) {
+                // the interpolation of mesorasi_interpolate3_add, in its fp32
+                // operations, then the addition and phi
+                const RrInterp& q = a.ip;
+                const int64_t r0 = rok ? row : 0;
+                const int64_t b = r0 / q.nd;
+                const float w0 = 1.0f / fmaxf(q.dist[r0 * 3 + 0], 1e-10f);
+                const float w1 = 1.0f / fmaxf(q.dist[r0 * 3 + 1], 1e-10f);
+                const float w2 = 1.0f / fmaxf(q.dist[r0 * 3 + 2], 1e-10f);
+                const float ws = w0 + w1 + w2;
+                const float u0 = w0 / ws, u1 = w1 / ws, u2 = w2 / ws;
+                const float* gs = q.g + b * q.ns * q.ldg;
+                const float* g0 = gs + (int64_t)q.nit[r0 * 3 + 0] * q.ldg;
+                const float* g1 = gs + (int64_t)q.nit[r0 * 3 + 1] * q.ldg;
+                const float* g2 = gs + (int64_t)q.nit[r0 * 3 + 2] * q.ldg;
+                const float* ad = q.add + r0 * q.lda;
+    #pragma unroll
+                for (int i = 0; i < kRrMaxSteps / 4; ++i) {
+                    if (4 * i < a.k0h) {
+                        const int k = kb + 8 * i;
+                        const bool ok = rok && k < a.c0;
+                        const int kk = ok ? k : 0;
+                        const float4 x0 = *reinterpret_cast<const float4*>(g0 + kk);
+                        const float4 x1 = *reinterpret_cast<const float4*>(g1 + kk);
+                        const float4 x2 = *reinterpret_cast<const float4*>(g2 + kk);
+                        const float4 p = *reinterpret_cast<const float4*>(ad + kk);
+                        float v[4] = {u0 * x0.x + u1 * x1.x + u2 * x2.x, u0 * x0.y + u1 * x1.y + u2 * x2.y,
+                                      u0 * x0.z + u1 * x1.z + u2 * x2.z, u0 * x0.w + u1 * x1.w + u2 * x2.w};
+                        v[0] += p.x;
+                        v[1] += p.y;
+                        v[2] += p.z;
+                        v[3] += p.w;
+    #pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            if (q.relu) v[e] = v[e] > 0.0f ? v[e] : 0.0f;
+                            dst[4 * i + e] = ok ? v[e] : 0.0f;
+                        }
+                    }
+                }
+            } else if (a.vec0) {
+                const float* src = a.x0 + (rok ? row : 0) * a.ld0;
+    #pragma unroll
+                for (int i = 0; i < kRrMaxSteps / 4; ++i) {
+                    if (4 * i < a.k0h) {
+                        const int k = kb + 8 * i;
+                        const bool ok = rok && k < a.c0;
+                        const float4 v = *reinterpret_cast<const float4*>(src + (ok ? k : 0));
+                        dst[4 * i + 0] = ok ? v.x : 0.0f;
+                        dst[4 * i + 1] = ok ? v.y : 0.0f;
+                        dst[4 * i + 2] = ok ? v.z : 0.0f;
+                        dst[4 * i + 3] = ok ? v.w : 0.0f;
+                    }
+                }
+            } else {
+                // [x0 | x1] element by element from clamped, in-bounds addresses
+                const int64_t r0 = rok ? row : 0;
+                const float* src0 = a.x0 + r0 * a.ld0;
+                const float* src1 = a.c1 > 0 ? a.x1 + r0 * a.ld1 : src0;
+    #pragma unroll
+                for (int i = 0; i < kRrMaxSteps; ++i) {
+                    if (i < a.k0h) {
+                        const int k = kb + 8 * (i >> 2) + (i & 3);
+                        const bool in0 = k < a.c0, in1 = !in0 && k < a.c0 + a.c1;
+                        const float v = in0 ? src0[k] : (in1 ? src1[k - a.c0] : src0[0]);
+                        dst[i] = (rok && (in0 || in1)) ? v : 0.0f;
+                    }
+                }
+            }
+}
+
 // Eight waves, two per SIMD: while one wave waits on its rows or runs its
 // epilogue, the other keeps the SIMD's MFMA pipe busy.  (A four-wave form
 // with 512 registers per wave that requested its next tile's rows before
@@ -386,74 +460,7 @@ void mlp_rr_kernel(RrArgs a) {
                 sm[e] = rok && k < a.cs ? v : 0.0f;
             }
         }
-        if (a.interp) {
-            // the interpolation of mesorasi_interpolate3_add, in its fp32
-            // operations, then the addition and phi
-            const RrInterp& q = a.ip;
-            const int64_t r0 = rok ? row : 0;
-            const int64_t b = r0 / q.nd;
-            const float w0 = 1.0f / fmaxf(q.dist[r0 * 3 + 0], 1e-10f);
-            const float w1 = 1.0f / fmaxf(q.dist[r0 * 3 + 1], 1e-10f);
-            const float w2 = 1.0f / fmaxf(q.dist[r0 * 3 + 2], 1e-10f);
-            const float ws = w0 + w1 + w2;
-            const float u0 = w0 / ws, u1 = w1 / ws, u2 = w2 / ws;
-            const float* gs = q.g + b * q.ns * q.ldg;
-            const float* g0 = gs + (int64_t)q.nit[r0 * 3 + 0] * q.ldg;
-            const float* g1 = gs + (int64_t)q.nit[r0 * 3 + 1] * q.ldg;
-            const float* g2 = gs + (int64_t)q.nit[r0 * 3 + 2] * q.ldg;
-            const float* ad = q.add + r0 * q.lda;
-#pragma unroll
-            for (int i = 0; i < kRrMaxSteps / 4; ++i) {
-                if (4 * i < a.k0h) {
-                    const int k = kb + 8 * i;
-                    const bool ok = rok && k < a.c0;
-                    const int kk = ok ? k : 0;
-                    const float4 x0 = *reinterpret_cast<const float4*>(g0 + kk);
-                    const float4 x1 = *reinterpret_cast<const float4*>(g1 + kk);
-                    const float4 x2 = *reinterpret_cast<const float4*>(g2 + kk);
-                    const float4 p = *reinterpret_cast<const float4*>(ad + kk);
-                    float v[4] = {u0 * x0.x + u1 * x1.x + u2 * x2.x, u0 * x0.y + u1 * x1.y + u2 * x2.y,
-                                  u0 * x0.z + u1 * x1.z + u2 * x2.z, u0 * x0.w + u1 * x1.w + u2 * x2.w};
-                    v[0] += p.x;
-                    v[1] += p.y;
-                    v[2] += p.z;
-                    v[3] += p.w;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        if (q.relu) v[e] = v[e] > 0.0f ? v[e] : 0.0f;
-                        dst[4 * i + e] = ok ? v[e] : 0.0f;
-                    }
-                }
-            }
-        } else if (a.vec0) {
-            const float* src = a.x0 + (rok ? row : 0) * a.ld0;
-#pragma unroll
-            for (int i = 0; i < kRrMaxSteps / 4; ++i) {
-                if (4 * i < a.k0h) {
-                    const int k = kb + 8 * i;
-                    const bool ok = rok && k < a.c0;
-                    const float4 v = *reinterpret_cast<const float4*>(src + (ok ? k : 0));
-                    dst[4 * i + 0] = ok ? v.x : 0.0f;
-                    dst[4 * i + 1] = ok ? v.y : 0.0f;
-                    dst[4 * i + 2] = ok ? v.z : 0.0f;
-                    dst[4 * i + 3] = ok ? v.w : 0.0f;
-                }
-            }
-        } else {
-            // [x0 | x1] element by element from clamped, in-bounds addresses
-            const int64_t r0 = rok ? row : 0;
-            const float* src0 = a.x0 + r0 * a.ld0;
-            const float* src1 = a.c1 > 0 ? a.x1 + r0 * a.ld1 : src0;
-#pragma unroll
-            for (int i = 0; i < kRrMaxSteps; ++i) {
-                if (i < a.k0h) {
-                    const int k = kb + 8 * (i >> 2) + (i & 3);
-                    const bool in0 = k < a.c0, in1 = !in0 && k < a.c0 + a.c1;
-                    const float v = in0 ? src0[k] : (in1 ? src1[k - a.c0] : src0[0]);
-                    dst[i] = (rok && (in0 || in1)) ? v : 0.0f;
-                }
-            }
-        }
+        rr_load_rows(a, row, rok, kb, dst);
     };
 
     // the first tile's rows are requested before the weights are staged,
@@ -593,7 +600,7 @@ void mlp_rr_kernel(RrArgs a) {
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[ob][r] = 0.0f;
         if (plain_w) {
-            rr_products_f32(nt, nob, reinterpret_cast<const float4*>(wl), act, acc);
+            rr_products_f32_any(nt, nob, reinterpret_cast<const float4*>(wl), act, acc);
         } else {
             // the row's largest value (NaN apart, whose parts are NaN)
             float top = 0.0f;
@@ -737,6 +744,162 @@ void mlp_rr_kernel(RrArgs a) {
     }
 }
 
+// Layers of at most 64 outputs, most of them of one block of 32, take the fp32
+// instruction throughout: the split of a row and the ten LDS reads of a step
+// would serve one or two blocks' products (rr_fp32_form).  All weights are in
+// LDS as fp32, in groups of four k steps.  Bound by the latency of a wave's one
+// or few tiles: rows from memory, a chain of products, rows to memory.
+template <int NJ, int NOB>
+__device__ __forceinline__ void rr_products_f32(const float4* __restrict__ wl, const float (&act)[kRrMaxSteps],
+                                                f32x16 (&acc)[2]) {
+#pragma unroll
+    for (int ob = 0; ob < NOB; ++ob)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[ob][r] = 0.0f;
+    float4 w[NOB];
+#pragma unroll
+    for (int ob = 0; ob < NOB; ++ob) w[ob] = wl[ob * 4 * NJ * 64];
+#pragma unroll
+    for (int g = 0; g < 4 * NJ; ++g) {
+        // the next group's weights are requested before this group's MFMAs
+        float4 wn[NOB];
+        if (g + 1 < 4 * NJ) {
+#pragma unroll
+            for (int ob = 0; ob < NOB; ++ob) wn[ob] = wl[(ob * 4 * NJ + g + 1) * 64];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int ob = 0; ob < NOB; ++ob)
+                acc[ob] = __builtin_amdgcn_mfma_f32_32x32x2f32((&w[ob].x)[e], act[4 * g + e], acc[ob], 0, 0, 0);
+        // keeps the compiler from hoisting every group's weights at once
+        __builtin_amdgcn_sched_barrier(0);
+        if (g + 1 < 4 * NJ) {
+#pragma unroll
+            for (int ob = 0; ob < NOB; ++ob) w[ob] = wn[ob];
+        }
+    }
+}
+
+__global__ __launch_bounds__(64 * kRrWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void mlp_rr_f32_kernel(RrArgs a) {
+    extern __shared__ float4 smem4[];
+    float* smem = reinterpret_cast<float*>(smem4);
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int hk = lane >> 5;
+
+    float act[kRrMaxSteps];
+    auto load_tile = [&](int64_t t) {
+        const int64_t row = t * 32 + (lane & 31);
+        int kb = 4 * hk;
+        asm volatile("" : "+v"(kb));
+        rr_load_rows(a, row, row < a.rows, kb, act);
+    };
+    const int64_t stride = (int64_t)gridDim.x * kRrWaves;
+    int64_t wg = blockIdx.x;
+    if (a.interp && (gridDim.x & 7) == 0) wg = (int64_t)(blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    const int64_t t0 = wg * kRrWaves + wave;
+    if (t0 < a.tiles) load_tile(t0);
+
+    // a layer's float4s, four consecutive k of one weight row each: at most 2
+    // blocks x 16 groups x 64 lanes, all of its loads in flight before the
+    // first LDS store
+    constexpr int kPer = 2 * 16 * 64 / (64 * kRrWaves);
+    for (int l = 0; l < a.n_layers; ++l) {
+        const int K = a.dims[l], N = a.dims[l + 1];
+        const int ng = 2 * rr_steps(a.dims, l, a.k0h);
+        const int total = rr_blocks(N) * ng * 64;
+        const unsigned inv = (65536u + ng - 1) / ng;   // gg / ng exactly for gg < 32
+        const float* __restrict__ W = a.W[l];
+        float4 v[kPer];
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            const int i = tid + 64 * kRrWaves * u;
+            const int ln = i & 63, gg = i >> 6;
+            const int ob = (int)(((unsigned)gg * inv) >> 16), g = gg - ob * ng;
+            const int n = ob * 32 + (ln & 31);
+            const int k = rr_k(l, 4 * g, ln >> 5);   // k .. k + 3 are consecutive
+            v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (i < total && n < N) {
+                const float* wr = W + (int64_t)n * K;
+                if (k + 4 <= K) {
+                    struct __attribute__((packed, aligned(4))) F4 { float x, y, z, w; };
+                    const F4 p = *reinterpret_cast<const F4*>(wr + k);
+                    v[u] = make_float4(p.x, p.y, p.z, p.w);
+                } else {
+                    v[u].x = k + 0 < K ? wr[k + 0] : 0.0f;
+                    v[u].y = k + 1 < K ? wr[k + 1] : 0.0f;
+                    v[u].z = k + 2 < K ? wr[k + 2] : 0.0f;
+                }
+            }
+        }
+        float4* dst = smem4 + (a.woff[l] >> 2);
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            const int i = tid + 64 * kRrWaves * u;
+            if (i < total) dst[i] = v[u];
+        }
+        const float* __restrict__ bs = a.bias[l];
+        for (int e = tid; e < rr_blocks(N) * 32; e += 64 * kRrWaves)
+            smem[a.boff[l] + e] = (bs && e < N) ? bs[e] : 0.0f;
+    }
+    __syncthreads();
+
+    for (int64_t t = t0; t < a.tiles; t += stride) {
+        const int64_t row = t * 32 + (lane & 31);
+        const bool rok = row < a.rows;
+        if (t != t0) load_tile(t);
+        for (int l = 0; l < a.n_layers; ++l) {
+            const int N = a.dims[l + 1];
+            const int nob = rr_blocks(N), nj = rr_steps(a.dims, l, a.k0h) / 2;
+            const float4* __restrict__ wl = smem4 + (a.woff[l] >> 2) + lane;
+            f32x16 acc[2];
+            switch (2 * nj + nob) {
+                case 3: rr_products_f32<1, 1>(wl, act, acc); break;
+                case 4: rr_products_f32<1, 2>(wl, act, acc); break;
+                case 5: rr_products_f32<2, 1>(wl, act, acc); break;
+                case 6: rr_products_f32<2, 2>(wl, act, acc); break;
+                case 7: rr_products_f32<3, 1>(wl, act, acc); break;
+                case 8: rr_products_f32<3, 2>(wl, act, acc); break;
+                case 9: rr_products_f32<4, 1>(wl, act, acc); break;
+                default: rr_products_f32<4, 2>(wl, act, acc); break;
+            }
+            const bool relu = (a.relu_mask >> l) & 1u, last = l + 1 == a.n_layers;
+            const float* __restrict__ bl = smem + a.boff[l] + 4 * hk;
+            float* yr = a.y + row * a.ldy;
+#pragma unroll
+            for (int ob = 0; ob < 2; ++ob) {
+                if (ob < nob) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const float4 b4 = *reinterpret_cast<const float4*>(bl + 32 * ob + 8 * q);
+                        float v[4] = {acc[ob][4 * q + 0] + b4.x, acc[ob][4 * q + 1] + b4.y,
+                                      acc[ob][4 * q + 2] + b4.z, acc[ob][4 * q + 3] + b4.w};
+                        if (relu) {
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) v[i] = rr_relu(v[i]);
+                        }
+                        const int c = 32 * ob + 8 * q + 4 * hk;
+                        if (!last) {
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) act[16 * ob + 4 * q + i] = v[i];
+                        } else if (rok) {
+                            if (a.vecy && c + 4 <= N) {
+                                *reinterpret_cast<float4*>(yr + c) = make_float4(v[0], v[1], v[2], v[3]);
+                            } else {
+#pragma unroll
+                                for (int i = 0; i < 4; ++i)
+                                    if (c + i < N) yr[c + i] = v[i];
+                            }
+                        }
+                    }
+                }
+            }
+        }
+    }
+}
+
 struct RrPlan {
     bool ok;
     int k0h;
@@ -777,6 +940,24 @@ RrPlan rr_plan(int n_layers, const int32_t* dims, int cs) {
     p.lds_floats = most + kRrWaves;
     p.ok = true;
     return p;
+}
+
+// All layers at most 64 wide and 3 F <= 5 S, F the output blocks' steps and S
+// the steps: the fp32 instruction (mlp_rr_f32_kernel), for sources without a
+// narrow one.  Measured, fp32 instruction against split, 65536 and 262144 rows:
+// F = S: 128 -> 32 16.2 / 18.8 and 50 / 53 us, 16 -> 8 x 32 23.3 / 31.7 and 66 /
+// 83; 128 -> 32 -> 32 -> 64 (14 : 12) 22.9 / 25.5 and 73 / 77; on the line, 128 ->
+// 64 -> 32, 23.5 / 25.1 and 76 / 72; beyond it 64 -> 64 -> 64 (2 : 1) 22.0 / 19.9
+// and 69 / 57, 128 -> 64 -> 64 27.8 / 25.3 and 92 / 77.
+bool rr_fp32_form(int n_layers, const int32_t* dims, int k0h) {
+    int f = 0, st = 0;
+    for (int l = 0; l < n_layers; ++l) {
+        const int nob = rr_blocks(dims[l + 1]), nt = rr_steps(dims, l, k0h);
+        if (nob > 2) return false;
+        f += nob * nt;
+        st += nt;
+    }
+    return 3 * f <= 5 * st;
 }
 
 hipError_t rr_lds_attr(void (*kernel)(RrArgs)) {
@@ -848,8 +1029,8 @@ int run_rr_mlp(const float* x0, int c0, int64_t ld0, const float* x1, int c1, in
     static const auto kernels = std::array<void (*)(RrArgs), 4>{
         &mlp_rr_kernel<false, false>, &mlp_rr_kernel<false, true>, &mlp_rr_kernel<true, false>,
         &mlp_rr_kernel<true, true>};
-    static const hipError_t attr[4] = {rr_lds_attr(kernels[0]), rr_lds_attr(kernels[1]), rr_lds_attr(kernels[2]),
-                                       rr_lds_attr(kernels[3])};
+    static const hipError_t attr[5] = {rr_lds_attr(kernels[0]), rr_lds_attr(kernels[1]), rr_lds_attr(kernels[2]),
+                                       rr_lds_attr(kernels[3]), rr_lds_attr(&mlp_rr_f32_kernel)};
     for (const hipError_t e : attr)
         MESO_REQUIRE(e == hipSuccess, MESORASI_EHIP, "mesorasi_pointwise_mlp: LDS size attribute: %s",
                      hipGetErrorString(e));
@@ -908,6 +1089,17 @@ int run_rr_mlp(const float* x0, int c0, int64_t ld0, const float* x1, int c1, in
     // the CUs (the kernel then orders tiles by XCD)
     int64_t grid = std::min<int64_t>(ceil_div(a.tiles, kRrWaves), cus);
     if ((a.interp || g) && 8 * ceil_div(grid, 8) <= cus) grid = 8 * ceil_div(grid, 8);
+    if (!g && cs == 0 && rr_fp32_form(n_layers, dims, pl.k0h)) {
+        int off = 0;   // at most 32 KB for the first layer and 16 for each other
+        for (int l = 0; l < n_layers; ++l) {
+            const int nob = rr_blocks(dims[l + 1]);
+            a.woff[l] = off;
+            a.boff[l] = off + nob * rr_steps(dims, l, pl.k0h) * 512;
+            off = a.boff[l] + nob * 32;
+        }
+        mlp_rr_f32_kernel<<<dim3((unsigned)grid), dim3(64 * kRrWaves), (size_t)off * sizeof(float), s>>>(a);
+        return after_launch("mesorasi_pointwise_mlp (register MLP, fp32 products)");
+    }
     const size_t lds = (size_t)pl.lds_floats * sizeof(float);
     kernels[(pl.nphase > 1 ? 2 : 0) + (g ? 1 : 0)]<<<dim3((unsigned)grid), dim3(64 * kRrWaves), lds, s>>>(a);
     return after_launch("mesorasi_pointwise_mlp (register MLP)");

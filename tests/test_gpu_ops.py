@@ -488,6 +488,14 @@ MLP_CASES = [
     ("rr_narrow_both", 33003, [5, 3], [33, 9], F32),
     ("rr_staged_136", 65536, [128, 8], [128, 128, 128], F32),   # the widest first layer, in phases
     ("rr_unaligned_out", 40000, [128], [98], F32),        # 98-float output rows: element stores
+    # at most 64 wide, most layers of one output block, no narrow source: fp32
+    # products; each number of input blocks with one and two output blocks
+    ("rr_fp32_128_head", 33000, [128], [32, 13], F32),
+    ("rr_fp32_elements", 33001, [20, 12], [32, 64, 17], F32),
+    ("rr_fp32_4_blocks_64", 65537, [128], [64, 32, 32, 32], F32),
+    ("rr_fp32_3_blocks_64", 40000, [95], [64, 32, 32, 32, 5], F32),
+    ("rr_fp32_3_blocks_32", 32769, [88], [29], F32),
+    ("rr_split_64_64", 33000, [128], [64, 64], F32),       # just past the rule: the split
     # the bf16 form (v_mfma_f32_32x32x16_bf16, activations packed in
     # registers)
     ("rr_bf16_two_src", 65536, [3, 3], [32, 32, 64], BF16),

@@ -1008,6 +1008,10 @@ bool rr_mlp_supported(const float* x0, int c0, int64_t ld0, const float* x1, int
                       const int32_t* dims, int64_t rows) {
     const int narrow = rr_narrow_source(x0, c0, ld0, x1, c1, ld1);
     if (narrow < 0) return rr_mlp_supported(n_layers, dims, rows);
+    // a single layer of more than 128 inputs, whose GEMM has no intermediate
+    // to keep from memory, is that GEMM (65536 x 131 -> 13, 32, 64: 15.6, 16.3,
+    // 18.5 us, here 18.5, 19.0, 21.1; 262144 x 131 -> 64: 56 against 69)
+    if (n_layers == 1 && dims[0] > kRrMaxWidth) return false;
     return rr_rows_ok(n_layers, dims, narrow == 2 ? dims[0] : narrow == 0 ? c0 : c1, rr_tiles_per_wave(rows));
 }
 

@@ -496,6 +496,7 @@ MLP_CASES = [
     ("rr_fp32_3_blocks_64", 40000, [95], [64, 32, 32, 32, 5], F32),
     ("rr_fp32_3_blocks_32", 32769, [88], [29], F32),
     ("rr_split_64_64", 33000, [128], [64, 64], F32),       # just past the rule: the split
+    ("gemm_single_131", 33000, [3, 128], [64], F32),       # one layer of more than 128 inputs: the GEMM
     # the bf16 form (v_mfma_f32_32x32x16_bf16, activations packed in
     # registers)
     ("rr_bf16_two_src", 65536, [3, 3], [32, 32, 64], BF16),

@@ -22,23 +22,30 @@
 // The fp32 matrix instruction bounded this kernel (65536 x 131 -> 128 -> 128
 // -> 128: 41 of 77 us; it runs at a sixteenth of the bf16 rate).  So every
 // fp32 value is taken as the exact sum of three bf16 values (24 = 3 x 8 bits
-// of mantissa, each part rounded to nearest) and a product as the six
-// partial products of at least 2^-18 of it, on v_mfma_f32_32x32x16_bf16 with
-// fp32 sums: eight k steps of a lane half make one of these instructions.
-// The three products left out are below 2^-25 of the product together, less
-// than the rounding of one fp32 sum, and there are fewer of those (six per
-// 16 k instead of sixteen).  The parts of huge values would overflow, those of
-// infinities would be NaN and those of very small ones denormal, and products
-// that overflow would meet others of the opposite sign.  So the weights and
-// each row's largest value are tested against a range in which none of this
-// occurs (kRrSmall).  Weights with one outside it are staged again as fp32 and
-// multiplied by v_mfma_f32_32x32x2_f32; so are the rows of a tile with one
-// outside it, by the weights' parts put together again (rr_products_plain).
+// of mantissa, each part rounded to nearest) and a product as the six largest
+// of its nine partial products, on v_mfma_f32_32x32x16_bf16 with fp32 sums:
+// eight k steps of a lane half make one of these instructions.
+// The three products left out are below 2^-24 of the product together (0.99
+// of that at w = x = 1 + 2^-8 - 2^-17): as much as the rounding of an fp32
+// product, which this form has besides.  It makes up for that with fewer
+// roundings of large sums (one per 16 k instead of eight).  2-norm error
+// against 64 bits, here and with the fp32 instruction: 16, 64 and 128 normal
+// values a row 3.4e-8, 4.6e-8, 6.2e-8 and 7.3e-8, 1.4e-7, 2.0e-7; half of them
+// 0: 3.3e-8, 4.1e-8, 5.1e-8 and 5.5e-8, 1.1e-7, 1.5e-7; but rows with a single
+// value that is not 0: 3.5e-8 and 2.5e-8 (at most 2.7 and 1.0 times 2^-24 of
+// it).  With two more of the partial products these last figures are 3.4e-8
+// and 2.0, and the kernel takes 6 to 15 % longer.
+// The parts of huge values would overflow, those of infinities would be NaN
+// and those of very small ones denormal, and products that overflow would
+// meet others of the opposite sign.  So the weights and each row's largest
+// value are tested against a range in which none of this occurs (kRrSmall).
+// Weights with one outside it are staged again as fp32 and multiplied by
+// v_mfma_f32_32x32x2_f32; so are the rows of a tile with one outside it, by
+// the weights' parts put together again (rr_products_plain).
 // Measured: 524288 gathered rows 3 -> 64 -> 64 -> 128, pooled: 128 -> 103 us;
-// 65536 x 131 -> 128 -> 128 -> 128: 77 -> 57 us with its launch; error against
-// 64 bits 1.3e-7 -> 7e-8 and 2.8e-7 -> 1.2e-7 (2-norm).  What bounds it now is
-// the split (44 vector instructions per 16 k of a row) and the LDS reads of the
-// weights, not yet the matrix cores (33 and 16 us).
+// 65536 x 131 -> 128 -> 128 -> 128: 77 -> 57 us with its launch.  What bounds
+// it now is the split (44 vector instructions per 16 k of a row) and the LDS
+// reads of the weights, not yet the matrix cores (33 and 16 us).
 // The first layer reads its rows straight from memory, the two lanes of a
 // row taking alternate 4-channel chunks.  Its input may have two parts: a
 // wide source of whole aligned 4-channel chunks, and a narrow one of at most
@@ -204,7 +211,8 @@ __device__ __forceinline__ void rr_small(const uint4 (&w)[2][3], const uint4 (&x
 // weights are requested ahead of the split of its activations or of the other
 // pair's products.  (The steps and blocks are guarded, not switched over: one
 // instance is in the kernel, and the activations keep their registers around
-// it; sixteen instances spilled them.)
+// it; sixteen instances spilled 200 to 800 of them, this one 4 and 16 in the
+// unphased forms and 23 and 30 in the phased ones.)
 __device__ __forceinline__ void rr_products(int nt, int nob, const uint4* __restrict__ wl, float (&act)[kRrMaxSteps],
                                             f32x16 (&acc)[kRrMaxWidth / 32]) {
     static_assert(kRrMaxWidth == 128, "two pairs of output blocks");

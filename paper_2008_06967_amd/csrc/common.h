@@ -112,6 +112,16 @@ __device__ __forceinline__ int wave_max_i32(int v) {
     return __builtin_amdgcn_readlane(v, 63);
 }
 
+// Compute units of the current device.
+inline int device_cus() {
+    int dev = 0, cus = 256;
+    if (hipGetDevice(&dev) == hipSuccess) {
+        int v = 0;
+        if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0) cus = v;
+    }
+    return cus;
+}
+
 // Float min / max over the wave (all lanes active), uniform result.
 template <int CTRL>
 __device__ __forceinline__ float dpp_f32(float v) {

@@ -32,8 +32,8 @@
 // (four waves per SIMD at 16 points per thread) and by the reduction chain
 // for small P.
 //
-// 128 and more samples of 257 to 16384 points: fps_rounds_kernel, which
-// selects many samples per exchange.  Fewer samples: from 513 to 8192 points
+// Many samples of 257 to 16384 points (fps_rounds_min): fps_rounds_kernel,
+// which selects several per exchange.  Fewer samples: from 513 to 8192 points
 // fps_lds_kernel keeps a copy of the coordinates in LDS as well, so the
 // winners are exchanged as (distance, index) and the new centroid is read from
 // LDS after the block reduction; from 8193 to 16384 points fps_skip_kernel
@@ -914,6 +914,7 @@ __global__ __launch_bounds__(T) void fps_rounds_kernel(const float* __restrict__
     int single = kFpsSingle;          // select one sample a round up to this many
     int tidx = 0, tinc = 0, level = -1;   // tied maxima: candidates at tau itself with lower indices than tidx
     int now = 0, par = 0;             // round % 3, round % 2
+    int last = 0;                     // the sample before a single round (-1: one of several)
 
     auto record = [&]() {
         if (wave == W - 1 && valid && lane < CAP && place < c) {
@@ -1020,9 +1021,10 @@ __global__ __launch_bounds__(T) void fps_rounds_kernel(const float* __restrict__
                 level = -1;
                 tau = max(v - step, 0);
             }
-            if (v <= 0) {
-                // every point coincides with a sample: nothing changes any
-                // more, and this one is every further sample
+            if (v <= 0 || sel == last) {
+                // every point coincides with a sample, or the last sample is
+                // the maximum again (a coordinate that is not finite): nothing
+                // changes any more, and this one is every further sample
                 if constexpr (XY) {
                     for (int o = m + tid; o < M; o += T) {
                         out_idx[o] = sel;
@@ -1038,6 +1040,7 @@ __global__ __launch_bounds__(T) void fps_rounds_kernel(const float* __restrict__
                 m = M;
                 break;
             }
+            last = sel;
         }
         if (m >= M) break;
         // rounds of several samples; at their start no running minimum is
@@ -1193,12 +1196,12 @@ __global__ __launch_bounds__(T) void fps_rounds_kernel(const float* __restrict__
         valid = false;
         c = 0;
         single = m + 1;
+        last = -1;
         if (n > 0) {
             tinc = max(1, (tidx > 0 ? tinc : N) * 22 / n);
             level = -1;
         } else {
             tinc = min(2 * tinc, N);
-            if (tidx == 0) top = tau;
         }
     }
     if constexpr (!XY) {
@@ -1510,6 +1513,32 @@ extern "C" size_t mesorasi_fps_workspace(int64_t B, int64_t N, int64_t M) {
     return fps_ws_bytes(B, N, M);
 }
 
+// From how many samples on a launch of B clouds of n points selects several of
+// them per round.  With fewer, the spatial sort (5 us at 1024 points, 20 us at
+// 16384) and the first samples, selected one at a time (0.6 to 1 us each), are
+// not won back (surfaces, here against one sample per iteration, 8 / 200
+// clouds: 512 points, 128 samples 35 / 36 against 38 / 39 us; 1024 points, 128
+// samples 42 / 46 against 41 / 42, 160 samples 45 / 49 against 51 / 52; 4096
+// points, 160 samples 73 / 82 against 80 / 80; 16384 points, 160 samples 163 /
+// 189 against 168 / 195).  Up to 256 points one wave without barriers is as
+// fast (250 points, 125 samples: 28 against 32 us).
+// With more clouds than CUs the time of a CU counts, which the rounds keep
+// busy, and fewer of their workgroups fit beside each other (1024 clouds: 512
+// points, 160 / 192 samples 82 / 87 against 74 / 88 us; 1024 points, 256
+// samples 117 against 128; 2048 points, 256 / 384 samples 269 / 312 against 208
+// / 309; 4096 points, 384 samples 409 against 490; 512 clouds of 8192 points,
+// 192 samples 222 against 281).
+// What the clouds hold is not known here.  Where most maxima are equal, or one
+// coordinate or one point spans the cloud (an integer grid, a line, a far
+// outlier), more rounds end with one sample, and one per iteration would be
+// faster up to 400 samples or so (4 clouds of 4096 points, 256 / 512 samples:
+// grid 179 / 236 against 122 / 239 us, line 152 / 199 against 123 / 240).
+static int64_t fps_rounds_min(int n, int64_t B) {
+    if (n <= 256 || n > 16384) return INT64_MAX;
+    if (B <= device_cus()) return n <= 512 ? 128 : 160;
+    return n <= 512 ? 192 : n <= 1024 ? 256 : n <= 4096 ? 384 : 192;
+}
+
 extern "C" int mesorasi_fps(const float* xyz, int64_t B, int64_t N, int64_t M, int32_t* idx, float* cxyz, void* ws,
                             size_t ws_bytes, void* stream) {
     MESO_REQUIRE(B >= 0 && N >= 0 && M >= 0, MESORASI_EINVAL, "mesorasi_fps: negative size (B=%lld N=%lld M=%lld)",
@@ -1532,14 +1561,7 @@ extern "C" int mesorasi_fps(const float* xyz, int64_t B, int64_t N, int64_t M, i
         if (pl.P == 8) return launch_fps_multi<8>(xyz, B, n, m, pl.G, idx, cxyz, ws, s);
         return launch_fps_multi<16>(xyz, B, n, m, pl.G, idx, cxyz, ws, s);
     }
-    // From 128 samples on, several per round: below, the spatial sort (5 us at
-    // 1024 points, 20 us at 16384) and the first samples, selected one at a
-    // time (0.6 to 1 us each), are not won back (96 / 128 samples, here against
-    // below: 500 points 30.2 / 33.8 against 29.2 / 38.2 us, 1024 36.5 / 39.9
-    // against 31.7 / 41.3, 4096 59.9 / 65.5 against 50.6 / 65.2, 16384 123 /
-    // 141 against 116 / 143).  Up to 256 points one wave without barriers is
-    // as fast (250 points, 125 samples: 28 against 32 us).
-    if (n > 256 && n <= 16384 && m >= 128) {
+    if (m >= fps_rounds_min(n, B)) {
         if (n <= 512) launch_fps_rounds<512, 1, 1>(xyz, B, n, m, idx, cxyz, s);
         else if (n <= 1024) launch_fps_rounds<512, 2, 2>(xyz, B, n, m, idx, cxyz, s);
         else if (n <= 2048) launch_fps_rounds<1024, 2, 2>(xyz, B, n, m, idx, cxyz, s);

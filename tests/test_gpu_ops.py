@@ -79,10 +79,40 @@ FPS_CASES = [
     ("skip_mesh", 2, 16384, 3000, "mesh"),
     ("skip_far_outlier", 1, 12000, 500, "outlier"),    # one point 1e6 away: a coarse grid
     ("lidar_sa1", 1, 16384, 4096, "lidar"),
-    # 257 .. 16384 points and 128 samples or more: several samples per round
+    # 257 .. 16384 points, fewer samples than several per round pay for: one
+    # sample per iteration, each workgroup shape at both ends of its clouds
+    ("iter_257_grid", 3, 257, 127, "grid"),            # 64 distinct points: ties, then zero steps
+    ("iter_512_dups", 2, 512, 120, "dups"),
+    ("iter_512_outlier", 2, 512, 127, "outlier"),
+    ("iter_513_grid", 2, 513, 100, "grid"),
+    ("iter_1000_dups", 2, 1000, 127, "dups"),
+    ("iter_1024_outlier", 2, 1024, 110, "outlier"),
+    ("iter_1025_dups", 2, 1025, 127, "dups"),
+    ("iter_2048_lattice", 2, 2048, 120, "lattice"),    # distinct points, nearly all maxima equal
+    ("iter_2049_grid", 2, 2049, 127, "grid"),
+    ("iter_4096_outlier", 2, 4096, 101, "outlier"),
+    ("iter_4097_dups", 2, 4097, 127, "dups"),
+    ("iter_8192_grid", 1, 8192, 126, "grid"),
+    ("iter_8192_outlier", 1, 8192, 127, "outlier"),
+    ("iter_skip_8193_dups", 1, 8193, 127, "dups"),
+    ("iter_skip_16384_grid", 1, 16384, 120, "grid"),
+    ("iter_skip_16384_outlier", 2, 16384, 127, "outlier"),
+    # both sides of the rule: by samples (up to 512 points and above), by clouds
+    ("rule_512_127", 2, 512, 127, "mesh"),
+    ("rule_512_128", 2, 512, 128, "mesh"),
+    ("rule_513_159", 2, 513, 159, "mesh"),
+    ("rule_513_160", 2, 513, 160, "mesh"),             # one point in the last row
+    ("rule_16384_160", 1, 16384, 160, "mesh"),
+    ("rule_many_512_191", 520, 300, 191, "mesh"),      # more clouds than CUs
+    ("rule_many_512_192", 520, 300, 192, "mesh"),
+    ("rule_many_1024_255", 300, 600, 255, "mesh"),
+    ("rule_many_1024_256", 300, 600, 256, "mesh"),
+    ("rule_many_2048_383", 270, 1100, 383, "normal"),
+    ("rule_many_2048_384", 270, 1100, 384, "normal"),
+    # several samples per round
     ("rounds_257", 3, 257, 257, "normal"),             # the smallest cloud; every point
     ("rounds_512_grid", 2, 512, 512, "grid"),          # 64 distinct points: equal maxima, then zeros
-    ("rounds_513", 2, 513, 128, "mesh"),               # one point in the last row; the fewest samples
+    ("rounds_513", 2, 513, 128, "mesh"),
     ("rounds_1024_lattice", 2, 1024, 700, "lattice"),  # distinct points, nearly all maxima equal
     ("rounds_1025_flat", 2, 1025, 600, "flat"),        # one axis constant
     ("rounds_2048_line", 2, 2048, 300, "line"),        # two axes constant
@@ -146,6 +176,29 @@ def test_fps_bit_exact(gpu, name, B, N, M, kind):
     assert np.array_equal(host(cxyz), rc)
     if need:
         assert int(ws[:4].view(torch.int32).item()) == 0     # no workgroup gave up waiting
+
+
+@pytest.mark.parametrize("N,M", [(500, 400), (1024, 500), (3000, 700), (8000, 600), (12000, 300)])
+@pytest.mark.parametrize("value", [np.nan, np.inf, -np.inf, 3.0e38])
+def test_fps_not_finite(gpu, value, N, M):
+    """Points whose distances are NaN or infinite: several samples per round
+    select the points that one sample per iteration does (the first 100, which
+    a launch of 100 samples takes in that form).  A NaN makes one point every
+    sample from some step on; an overflow leaves its point at distance 0 from
+    itself."""
+    x = g(3).standard_normal((2, N, 3)).astype(np.float32)
+    x[:, 7, 1] = value
+    x[1, [N // 2, N - 1], 2] = value
+    few, _ = ops.fps(dev(x), 100)
+    idx, cxyz = ops.fps(dev(x), M)
+    idx = host(idx)
+    assert np.array_equal(idx[:, :100], host(few))
+    assert np.array_equal(host(cxyz), np.take_along_axis(x, idx[..., None].astype(np.int64), 1), equal_nan=True)
+    if np.isfinite(value):
+        ri, _ = O.fps(x, M)
+        assert np.array_equal(idx, ri)
+    elif np.isnan(value):
+        assert (idx[:, 100:] == idx[:, 99:100]).all()
 
 
 FPS_PREFIX_CASES = [

@@ -9,8 +9,9 @@
 // stops after the step that completes K hits (the early exit is what makes
 // dense surface-like clouds cheap), then the tail of the row is padded with
 // the first hit.  Clouds of 2048 to 8191 points are first copied into LDS
-// by a workgroup that serves 16 queries; from 8192 points a grid of cells
-// bounds the candidates.
+// by a workgroup that serves 16 queries.  Many queries of 1025 to 8191 points
+// are answered from cells that every workgroup builds in LDS; from 8192 points
+// a grid of cells in memory bounds the candidates.
 #include <algorithm>
 #include <cmath>
 #include <type_traits>
@@ -407,8 +408,10 @@ __global__ __launch_bounds__(64 * kGridQWaves) void grid_query_kernel(const floa
 // the same exactness) in its own LDS -- rebuilding it in each workgroup costs
 // less than a launch -- and then tests, for each query, only the points of
 // the 27 cells around it.  The cells' points, the cell ends and the hit
-// bitmaps are all read at LDS latency, and the workgroups number at most one
-// per CU, each serving `per` queries.  A query takes GL lanes: 16 where four
+// bitmaps are all read at LDS latency.  The workgroups number at most one per
+// CU, whole ones per cloud, each serving `per` queries (with more than half as
+// many clouds as CUs one each: a CU's registers hold one, so a second would
+// repeat the cells and wait).  A query takes GL lanes: 16 where four
 // bitmaps per wave fit (its nine rows of cells hold some ten points each), a
 // whole wave for the larger clouds.
 // ---------------------------------------------------------------------------
@@ -422,7 +425,12 @@ constexpr int64_t kBqCellMaxN = 8191;
 // points, 16384 queries, r = 0.1 walk 34.6 / cells 19.2 us, r = 0.4 19.4 /
 // 18.4; 32 x 1500, 22400 queries 22.7 / 15.8; 4 x 8191, 8192 queries 39.6 /
 // 25.8; 16 x 8000, 32000 queries, K = 64 142 / 72; below, 4 x 4096, 4096
-// queries 13.1 / 16.8).
+// queries 13.1 / 16.8).  What the walk loses here is waves, 16 per CU: dense
+// balls on smaller clouds take up to 1.3 times as long (10 x 2539, r = 0.4 19.7
+// / 23.7; 22 x 1206, K = 16, r = 0.4 17.3 / 22.7), as does a cloud that a far
+// point leaves in one cell, for the cells it builds first (16 x 4096, r = 0.1
+// 28.2 / 38.7); sparse ones a half to a quarter (32 x 4096, r = 0.1 57.6 / 18.5,
+// 256 x 4096 431 / 75).
 constexpr int64_t kBqCellMinSteps = 60000;
 constexpr float kBqDense = 0.7f;          // of the candidates at which one query's walk costs the same
 
@@ -761,15 +769,6 @@ __global__ __launch_bounds__(64 * kBqCellWaves) void ball_query_cells_kernel(
     }
 }
 
-static int bq_cus() {
-    int dev = 0, cus = 256;
-    if (hipGetDevice(&dev) == hipSuccess) {
-        int v = 0;
-        if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0) cus = v;
-    }
-    return cus;
-}
-
 // walk or grid: a ball of c candidates holds about 0.155 c points (sphere over
 // 27 cubes), so a walk scans about K N / (0.155 c); the two cost the same near
 // c = sqrt(6.45 K N).  With 16 lanes per query the walks of a wave's four
@@ -781,10 +780,8 @@ static int bq_walk_above(int64_t N, int32_t K, int lanes = 64) {
 
 static int launch_bq_cells(const float* xyz, const float* qxyz, int64_t B, int64_t N, int64_t M, float radius,
                            int32_t K, int32_t* nit, int32_t* cnt, hipStream_t s, const char* who) {
-    // one workgroup per CU, a multiple of 16 waves' queries each
-    const int lanes = bq_cell_lanes(N), at_once = kBqCellWaves * 64 / lanes;
-    const int64_t share = std::max<int64_t>(1, bq_cus() / B);
-    const int64_t per = ceil_div(ceil_div(M, share), at_once) * at_once;
+    const int64_t share = std::max<int64_t>(1, device_cus() / B);
+    const int64_t per = ceil_div(M, share);
     const int64_t wgs = ceil_div(M, per);
     MESO_REQUIRE(B * wgs <= 0x7fffffff, MESORASI_EUNSUPPORTED, "%s: too many queries", who);
     auto launch = [&](auto lanes_c, auto points_c) {

@@ -275,17 +275,23 @@ BQ_CASES = [
     ("grid_two_far_clusters", 1, 12000, 400, 0.05, 16, "clusters"),   # 32 cells per axis cap: cells wider than r
     ("grid_queries_outside", 2, 8192, 300, 0.5, 32, "outside"),
     ("grid_n_max", 1, 65536, 256, 0.1, 64, "normal"),
-    # many queries of 1025 .. 8191 points: cells in LDS, 16 lanes or a wave per query
+    # many queries of 1025 .. 8191 points: cells in LDS, 16 lanes or a wave per
+    # query; or, where the workgroup finds its balls dense, the index-order walk
     ("cells_1025", 20, 1025, 1025, 0.3, 16, "normal"),
-    ("cells_2048_grid", 16, 2048, 1000, 1.0, 32, "grid"),      # points at exactly distance r
+    ("cells_2048_grid", 16, 2048, 1000, 1.0, 32, "grid"),      # walks (64 distinct points), some at exactly distance r
     ("cells_4096_mesh", 8, 4096, 1024, 0.1, 32, "mesh"),
     ("cells_4096_k1", 8, 4096, 1030, 0.1, 1, "cube"),
     ("cells_4097_k1024", 8, 4097, 1000, 0.9, 1024, "normal"),
     ("cells_4500_dense", 7, 4500, 1000, 3.0, 64, "mesh"),      # every ball dense: the index-order walk
     ("cells_5120_outside", 6, 5120, 1100, 0.7, 32, "outside"),
-    ("cells_5121_clusters", 6, 5121, 1000, 0.05, 32, "clusters"),
-    ("cells_6145_outlier", 6, 6145, 1000, 0.3, 32, "outlier"),  # all but one point in one cell
-    ("cells_8191_dups", 4, 8191, 1000, 0.2, 64, "dups"),
+    ("cells_5121_clusters", 6, 5121, 1000, 0.05, 32, "clusters"),   # walks: two cells hold all points
+    ("cells_6145_outlier", 6, 6145, 1000, 0.3, 32, "outlier"),  # walks: all but one point in one cell
+    ("cells_8191_dups", 4, 8191, 1000, 0.2, 64, "dups"),       # a fifth of the queries dense: these walk
+    ("cells_4096_lattice", 16, 4096, 1024, 1.0, 32, "lattice"),   # cells 1.7 r wide; points at exactly distance r
+    ("cells_7000_lattice", 8, 7000, 1000, 1.0, 32, "lattice"),    # cells 2.4 r wide
+    ("cells_2500_knot", 5, 2500, 2500, 0.02, 1, "knot"),       # 59 or more waves with dense and other queries
+    ("cells_8000_wide", 6, 8000, 1000, 0.01, 16, "cube"),      # cells 19 r wide, no dense query
+    ("cells_130_clouds", 130, 1100, 200, 0.2, 32, "cube"),     # one workgroup per cloud
 ]
 
 
@@ -320,6 +326,12 @@ def test_ball_query_bit_exact(gpu, name, B, N, M, r, K, kind):
         x = x.astype(np.float32)
     elif kind == "outside":
         x = rr.standard_normal((B, N, 3)).astype(np.float32)
+    elif kind == "knot":       # a uniform cube with a quarter of the points in its middle
+        x = rr.uniform(0.0, 1.0, (B, N, 3))
+        for b in range(B):
+            i = rr.permutation(N)[:N // 4]
+            x[b, i] = 0.5 + rr.uniform(-0.13, 0.13, (len(i), 3))
+        x = x.astype(np.float32)
     else:
         x = _points(kind, B, N, rr)
     if kind in ("grid", "normal") and name != "nohit":

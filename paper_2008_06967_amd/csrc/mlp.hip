@@ -908,16 +908,31 @@ static bool use_fused(int64_t rows, int n_layers, const int32_t* dims, int dtype
 
 // The register-resident MLP (mlp_rr.hip, mlp_rr_bf16.hip) for plain rows.
 // fp32: above that count when every layer is at most 128 wide (65536 x 131 ->
-// 128 -> 128 -> 128: 57 us against 100 for the GEMM layers).
-// bf16: the GEMM's launches and HBM round trips per layer dominate.  Up to 96
-// KB of weights, staged by every workgroup, it wins from 1024 rows on (1024 x
-// 131 -> 64 -> 64 -> 128: 17.2 against 21.0 us; 65536 rows: 24 against 43);
-// with more, only from many rows on (131 -> 128 -> 128 -> 256: 4096 rows 27.3
-// against 21.4, 32768 rows 30.8 against 41.2, 65536 rows 36 against 62; at
-// 16384 rows 3 -> 128 -> 128 -> 256 still loses, 22.5 against 20.7).
+// 128 -> 128 -> 128: 57 us against 100 for the GEMM layers; 128 -> 128 -> 128,
+// staged in phases, 65536 rows 47 against 54, 262144 rows 155 against 173).  It
+// would already win below (131 -> 64 -> 64 -> 128: 32768 rows 35 us in the fused
+// kernel, 33000 rows 29 here), but mesorasi_aggregate_mlp runs the fused kernel
+// and gives the result of this entry point on the aggregated rows bit for bit.
+// bf16: the GEMM's launches and HBM round trips per layer dominate from 16385
+// rows on (131 -> 64 -> 64 -> 128: 20000 rows 15.5 against 21.9 us, 32768 16.4
+// against 23.5; 131 -> 128 -> 128 -> 256: 32768 rows 31.5 against 42.4; at 24576
+// rows, which fill the GEMM's tiles, 128 -> 128 -> 128 loses, 15.2 against 12.6).
+// With fewer rows both wait: the register MLP for its weights, which every
+// workgroup stages before the first product, the GEMMs for each other.  It takes
+// those of up to 48 KB of weights that save two launches or the element loads of
+// [narrow | wide] rows (4096 rows in a replayed graph, and called one after
+// another where launches count: 131 -> 64 -> 64 -> 128 14.1 against 13.7 and 14.2
+// against 17.8 us; 131 -> 64 -> 64 12.4 against 14.4 and 12.9 against 15.3; 3 ->
+// 32 -> 32 -> 64 10.9 against 9.6 and 12.3 against 16.9), not the others (6 -> 64
+// -> 128 10.7 against 7.3 and 12.4 against 14.3; 128 -> 128 -> 128 12.8 against
+// 8.8 and 13.0 against 14.4).
+// A single bf16 layer has no intermediate: its GEMM is the faster one (33000 /
+// 262144 rows, 32 -> 128 6.4 / 29 against 11.5 / 39 us, 16 -> 16 3.9 / 11.9
+// against 6.4 / 13.1).
 constexpr int64_t kRrMinRows = kFusedMaxPlainRows + 1;
-constexpr int64_t kRbMinRows = 1024, kRbMinRowsWide = 16385;
-constexpr int kRbFewWeights = 98 * 1024;   // (96 KB and the biases)
+constexpr int64_t kRbFewRows = 1024, kRbManyRows = 16385;
+constexpr int kRbFewWeights = 49 * 1024;   // (48 KB and the biases)
+constexpr int kRbShortInput = 32;          // (the element loader's, of any sources)
 static bool use_rr(const float* x0, int c0, int64_t ld0, const float* x1, int c1, int64_t ld1, int64_t rows,
                    int n_layers, const int32_t* dims, int dtype, int out_dtype, int64_t pool_group,
                    bool neighbor_rows) {
@@ -925,17 +940,20 @@ static bool use_rr(const float* x0, int c0, int64_t ld0, const float* x1, int c1
     if (dtype == MESORASI_F32)
         return rows >= kRrMinRows && out_dtype == MESORASI_F32 &&
                rr_mlp_supported(x0, c0, ld0, x1, c1, ld1, n_layers, dims, rows);
-    if (dtype != MESORASI_BF16 || rows < kRbMinRows || n_layers < 2) return false;
+    if (dtype != MESORASI_BF16 || rows < kRbFewRows || n_layers < 2) return false;
     const int lds = rb_mlp_lds_bytes(x0, c0, ld0, x1, c1, ld1, n_layers, dims);
-    return lds > 0 && (lds <= kRbFewWeights || rows >= kRbMinRowsWide);
+    if (lds == 0 || rows >= kRbManyRows) return lds > 0;
+    return lds <= kRbFewWeights && (n_layers > 2 || (x1 && c1 > 0 && dims[0] > kRbShortInput));
 }
 
 // Gathered neighbor rows pooled over 16 or 32 of them take the register MLP
 // from this count on, one tile per wave of a chip's persistent workgroups
-// (3 -> 64 -> 64 -> 128: 65536 rows 26 against 38 us fused, 524288 rows 144
-// against 217 with 32 per centroid and 75 against 300 with 16, whose atomic
-// max per half tile is what the fused kernel spends its time on); with fewer
-// rows, waves stay empty and the fused kernel is as fast.
+// (3 -> 64 -> 64 -> 128: 65536 rows 18.7 against 35.3 us fused with 32 per
+// centroid and 20.2 against 88.3 with 16, whose atomic max per half tile is
+// what the fused kernel spends its time on, 524288 rows 103 against 205 and 102
+// against 578; 3 -> 128 -> 128 -> 128, staged in phases: 65536 rows 36 against
+// 54, 524288 rows 251 against 390); with fewer rows, waves stay empty and the
+// fused kernel is as fast.
 constexpr int64_t kRrMinPooledRows = 65536;
 
 static size_t mlp_ws_bytes(int64_t rows, int n_layers, const int32_t* dims, int dtype, bool neighbor_rows) {

@@ -552,6 +552,11 @@ MLP_CASES = [
     ("rr_narrow_alone", 33000, [8], [32, 16], F32),
     ("rr_narrow_both", 33003, [5, 3], [33, 9], F32),
     ("rr_staged_136", 65536, [128, 8], [128, 128, 128], F32),   # the widest first layer, in phases
+    # 106 to 160 KB of fp32 weights: two phases, several tiles per wave, the
+    # last ones without every wave or row
+    ("rr_staged_tiles", 131073, [128], [128, 128], F32),
+    ("rr_staged_tiles_narrow", 70001, [3, 64], [96, 96, 128], F32),
+    ("rr_staged_tiles_ragged", 150000, [100], [128, 97], F32),
     ("rr_unaligned_out", 40000, [128], [98], F32),        # 98-float output rows: element stores
     # at most 64 wide, most layers of one output block, no narrow source: fp32
     # products; each number of input blocks with one and two output blocks
@@ -573,7 +578,15 @@ MLP_CASES = [
     ("rr_bf16_narrow_first", 40001, [3, 128], [128, 128, 256], BF16),
     ("rr_bf16_narrow_last", 2049, [36, 7], [100, 129], BF16),
     ("rr_bf16_wide_odd_out", 1025, [128], [64, 161], BF16),
-    ("rr_bf16_lds_limit", 4096, [8, 64], [128, 128, 128, 256], BF16),
+    ("rr_bf16_lds_limit", 4096, [8, 64], [128, 128, 128, 256], BF16),        # (few rows for its weights: the GEMM)
+    ("rr_bf16_lds_limit_ragged", 16385, [8, 64], [128, 128, 128, 256], BF16),   # 154 KB of weights, one row over
+    # both sides of the rule for few rows: by weights, sources, layers and rows
+    ("rr_bf16_1024_short", 1024, [3], [32, 32, 64], BF16),
+    ("gemm_bf16_1023_short", 1023, [3], [32, 32, 64], BF16),
+    ("rr_bf16_1024_two_layers", 1024, [3, 128], [64, 64], BF16),
+    ("gemm_bf16_1024_two_layers", 1024, [128], [128, 128], BF16),
+    ("gemm_bf16_1025_wide", 1025, [128], [128, 128, 64], BF16),              # above 48 KB
+    ("gemm_bf16_single", 33001, [32], [128], BF16),
 ]
 
 
@@ -772,6 +785,10 @@ CONV_CASES = {
     "rr_pool_k16_half_tile": (9, 600, 457, 16, 0, [33, 20], F32, 0),
     "rr_pool_feat": (4, 512, 512, 32, 64, [64, 100], F32, 0),
     "rr_pool_k16_strided": (8, 512, 512, 16, 4, [32, 128], F32, 12),
+    # weights in two phases, several tiles per wave, half tiles at the end
+    "rr_pool_phased_xyz": (4, 600, 520, 32, 0, [128, 128, 128], F32, 0),
+    "rr_pool_phased_tiles": (9, 600, 457, 32, 0, [128, 128, 100], F32, 0),
+    "rr_pool_phased_k16": (9, 600, 457, 16, 128, [128, 96], F32, 0),
 }
 
 

@@ -914,7 +914,7 @@ __global__ __launch_bounds__(T) void fps_rounds_kernel(const float* __restrict__
     int single = kFpsSingle;          // select one sample a round up to this many
     int tidx = 0, tinc = 0, level = -1;   // tied maxima: candidates at tau itself with lower indices than tidx
     int now = 0, par = 0;             // round % 3, round % 2
-    int last = 0;                     // the sample before a single round (-1: one of several)
+    int last = -1;                    // the last sample while the maximum is infinite
 
     auto record = [&]() {
         if (wave == W - 1 && valid && lane < CAP && place < c) {
@@ -974,11 +974,40 @@ __global__ __launch_bounds__(T) void fps_rounds_kernel(const float* __restrict__
         }
     };
 
+    // s is every further sample
+    auto repeat = [&](int sel) {
+        if constexpr (XY) {
+            for (int o = m + tid; o < M; o += T) {
+                out_idx[o] = sel;
+                if (out_c) {
+                    out_c[3 * o + 0] = s.x;
+                    out_c[3 * o + 1] = s.y;
+                    out_c[3 * o + 2] = s.z;
+                }
+            }
+        } else {
+            for (int o = m + tid; o < M; o += T) s_out[o] = (uint16_t)sel;
+        }
+        m = M;
+    };
+
     for (;;) {
         // single rounds: the largest running minimum, the lowest index holding it
         for (;;) {
             record();
-            if (m >= M || m >= single) break;
+            if (m >= M) break;
+            if (m >= single) {
+                // +inf (a coordinate that is not finite, or differences that
+                // overflow) may stay the maximum when selected, which only a
+                // single round gets right; selected twice in a row it stays
+                if (dmax != __float_as_int(inf)) break;
+                const int sel = __builtin_amdgcn_readfirstlane(__float_as_int(s.w));
+                if (sel == last) {
+                    repeat(sel);
+                    break;
+                }
+                last = sel;
+            }
             update();
             int b1 = dm[0], bi = index(0);
 #pragma unroll
@@ -1008,10 +1037,6 @@ __global__ __launch_bounds__(T) void fps_rounds_kernel(const float* __restrict__
             place = 0;
             c = 1;
             dmax = top = v;
-            // +inf (a coordinate that is not finite, or differences that
-            // overflow) may stay the maximum when selected, which only a
-            // single round gets right
-            if (v == __float_as_int(inf)) single = m + 2;
             if (tinc > 0 && (level < 0 || v == level)) {
                 level = v;
                 tau = v;
@@ -1021,26 +1046,12 @@ __global__ __launch_bounds__(T) void fps_rounds_kernel(const float* __restrict__
                 level = -1;
                 tau = max(v - step, 0);
             }
-            if (v <= 0 || sel == last) {
-                // every point coincides with a sample, or the last sample is
-                // the maximum again (a coordinate that is not finite): nothing
-                // changes any more, and this one is every further sample
-                if constexpr (XY) {
-                    for (int o = m + tid; o < M; o += T) {
-                        out_idx[o] = sel;
-                        if (out_c) {
-                            out_c[3 * o + 0] = s.x;
-                            out_c[3 * o + 1] = s.y;
-                            out_c[3 * o + 2] = s.z;
-                        }
-                    }
-                } else {
-                    for (int o = m + tid; o < M; o += T) s_out[o] = (uint16_t)sel;
-                }
-                m = M;
+            if (v <= 0) {
+                // every point coincides with a sample: nothing changes any
+                // more, and this one is every further sample
+                repeat(sel);
                 break;
             }
-            last = sel;
         }
         if (m >= M) break;
         // rounds of several samples; at their start no running minimum is
@@ -1196,7 +1207,6 @@ __global__ __launch_bounds__(T) void fps_rounds_kernel(const float* __restrict__
         valid = false;
         c = 0;
         single = m + 1;
-        last = -1;
         if (n > 0) {
             tinc = max(1, (tidx > 0 ? tinc : N) * 22 / n);
             level = -1;

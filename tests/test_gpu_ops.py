@@ -60,7 +60,8 @@ FPS_CASES = [
     ("seg_sa1", 2, 4096, 1024, "normal"),
     ("n2000", 2, 2000, 700, "normal"),
     ("n9000", 1, 9000, 300, "normal"),
-    # 513 .. 16384 points: the cloud's coordinates in LDS
+    # 513 .. 8192 points (with fewer than 160 samples the cloud's coordinates in
+    # LDS, one sample per iteration)
     ("lds_smallest_m_eq_n", 3, 513, 513, "normal"),
     ("lds_four_waves_grid", 2, 1000, 1000, "grid"),     # four waves: the block max over four slots
     ("lds_1025_m_eq_n", 3, 1025, 1025, "normal"),
@@ -68,7 +69,8 @@ FPS_CASES = [
     ("lds_m65", 2, 2048, 65, "mesh"),                  # one result block plus one
     ("lds_grid_ties", 2, 4096, 1500, "grid"),          # 64 distinct points: ties across waves, zero steps
     ("lds_dups", 1, 8192, 2048, "dups"),
-    # 8193 .. 16384 points: spatial order, updates skipped by the box bound
+    # 8193 .. 16384 points: spatial order, updates skipped by the box bound (one
+    # sample per iteration below 160 samples)
     ("skip_grid_ties", 1, 12000, 700, "grid"),         # equal distances across lanes and waves
     ("skip_ragged", 3, 8193, 300, "normal"),           # one real point in the last thread
     ("skip_m_eq_n", 1, 9000, 9000, "normal"),          # every point, minima down to 0
